@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/nttmi.h"
+#include "i8plan.hpp"
 #include "launch.hpp"
 #include "numtheory.hpp"
 
@@ -24,6 +25,8 @@ struct Plan {
     double2* dP = nullptr;
     double* dTT = nullptr;
     uint32_t* dTT32 = nullptr;
+    int8_t* dI8 = nullptr;   // tables of the matrix-core kernels
+    I8Plan i8{};             // (tab null: no such kernel for this plan)
 };
 
 struct Buf {
@@ -234,16 +237,23 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
             he = upload(&p.dTT32, t32);
         }
     }
-    if (he != hipSuccess) {
-        if (p.dP) (void)hipFree(p.dP);
-        if (p.dTT) (void)hipFree(p.dTT);
-        if (p.dTT32) (void)hipFree(p.dTT32);
-        return hip_status(he);
-    }
     // N^-1 mod m, the multiplicative inverse of N (Appendix A): 2^(nu - n)
     // when 2 has order nu = 2^lnu, else N^(m - 2) (Fermat, m prime)
     const uint64_t ninv = (l2 >= (int)log2n) ? powmod64(2, (1ull << l2) - log2n, m)
                                              : powmod64((1ull << log2n) % m, m - 2, m);
+    if (he == hipSuccess && m <= I8_MAX_M && (int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WAVE_MAX_LOG2N) {
+        const std::vector<int8_t> t = i8_wave_tables((int)log2n, m, ninv, [&](uint64_t e) { return (uint64_t)hP[e].x; },
+                                                     &p.i8.C);
+        he = upload(&p.dI8, t);
+        p.i8.tab = p.dI8;
+    }
+    if (he != hipSuccess) {
+        if (p.dP) (void)hipFree(p.dP);
+        if (p.dTT) (void)hipFree(p.dTT);
+        if (p.dTT32) (void)hipFree(p.dTT32);
+        if (p.dI8) (void)hipFree(p.dI8);
+        return hip_status(he);
+    }
     (void)lnu;
     p.dev.P = p.dP;
     p.dev.TT = p.dTT;
@@ -509,6 +519,8 @@ ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f
     hipStream_t s = (hipStream_t)stream;
     if ((int)log2n <= SMALL_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
+        if (wbits == 32 && p->i8.tab)
+            return hip_status(launch_conv_wave((int)log2n, f, g, h, 1, p->i8, (uint32_t)cu_count(), s));
         return hip_status(launch_conv_small((int)wbits, log2n, f, g, h, nullptr, 1, p->dev, s));
     }
     void* ws = nullptr;
@@ -572,6 +584,9 @@ ntt_status launch_items(uint32_t n, uint32_t c, uint64_t base, const uint64_t* d
     ntt_status st = NTT_OK;
     if ((int)n <= SMALL_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
+        if (elem_bits == 32 && p->i8.tab && contiguous && form == CF_DEFAULT)
+            return hip_status(launch_conv_wave((int)n, F + base * wb, G + base * wb, H + base * wb, c, p->i8,
+                                               (uint32_t)cu_count(), s));
         return hip_status(launch_conv_small((int)elem_bits, n, F + base * wb, G + base * wb, H + base * wb, doffs, c,
                                             p->dev, s, form == CF_SMALL_WAVE ? SMALL_TILE_WAVE : SMALL_TILE_256));
     }
@@ -940,6 +955,8 @@ ntt_status conv_circular_noalloc(uint64_t m, uint32_t log2n, uint64_t root, uint
     hipStream_t s = (hipStream_t)stream;
     if (!fourstep) {
         count(NTT_COUNT_SMALL);
+        if (elem_bits == 32 && p->i8.tab)
+            return hip_status(launch_conv_wave((int)log2n, f, g, h, 1, p->i8, (uint32_t)cu_count(), s));
         return hip_status(launch_conv_small((int)elem_bits, log2n, f, g, h, nullptr, 1, p->dev, s));
     }
     void* ws = nullptr;
@@ -1347,6 +1364,7 @@ void ntt_release_caches(void) {
         if (kv.second.dP) (void)hipFree(kv.second.dP);
         if (kv.second.dTT) (void)hipFree(kv.second.dTT);
         if (kv.second.dTT32) (void)hipFree(kv.second.dTT32);
+        if (kv.second.dI8) (void)hipFree(kv.second.dI8);
     }
     c.plans.clear();
     for (auto& kv : c.work) if (kv.second.ptr) (void)hipFree(kv.second.ptr);

@@ -1,0 +1,123 @@
+// Host side of the matrix-core transforms: constants and tables of one plan.
+#pragma once
+#include <cstring>
+#include <vector>
+
+#include "launch.hpp"
+#include "numtheory.hpp"
+
+namespace nttmi {
+
+// The signed digits of a residue: three of the representative that fits them
+// (any window of m <= 2^24 consecutive integers from -8421504 on does).
+inline void i8_digits(uint64_t x, uint64_t m, int8_t d[3]) {
+    int64_t v = (int64_t)(x % m);
+    if (v > 8355711) v -= (int64_t)m;
+    for (int c = 0; c < 3; ++c) {
+        d[c] = (int8_t)(uint8_t)(v & 255);
+        v = (v - d[c]) >> 8;
+    }
+}
+
+// Appends the fragments of a 16 x 16 matrix (row: output, column: input) in the
+// lanes' order: plane c, lane l = 16 g + row, bytes 4 i + a the digit c of
+// 256^a M[row][4 g + i].
+template <class F>
+inline void i8_matrix(std::vector<int8_t>& out, uint64_t m, F entry) {
+    const size_t at = out.size();
+    out.resize(at + 3 * 64 * 16);
+    for (int l = 0; l < 64; ++l)
+        for (int i = 0; i < 4; ++i) {
+            uint64_t x = entry(l & 15, 4 * (l >> 4) + i) % m;
+            for (int a = 0; a < 4; ++a) {
+                int8_t d[3];
+                i8_digits(x, m, d);
+                for (int c = 0; c < 3; ++c) out[at + (size_t)(c * 64 + l) * 16 + 4 * i + a] = d[c];
+                x = mulmod64(x, 256, m);
+            }
+        }
+}
+
+inline void i8_pair(std::vector<int8_t>& out, uint64_t w, uint64_t m) {
+    int64_t b = (int64_t)(w % m);
+    if (2 * b > (int64_t)m) b -= (int64_t)m;
+    const int32_t wi = (int32_t)b;
+    const float wq = (float)(-(double)b / (double)m);
+    const size_t at = out.size();
+    out.resize(at + 8);
+    std::memcpy(&out[at], &wi, 4);
+    std::memcpy(&out[at + 4], &wq, 4);
+}
+
+// radix: of the first step (the correction for raw words)
+inline I8C make_i8c(uint64_t m, int radix) {
+    I8C C{};
+    const uint32_t mu = (uint32_t)m, dig = 0x80808080u;
+    C.m = mu;
+    C.small = m < (1u << 21) ? 1u : 0u;
+    C.k16 = (float)(-65536.0 / (double)m);
+    C.mg2 = (float)(12582912.0 - 12582912.0 * (double)C.k16);
+    C.k8 = (float)(-256.0 / (double)m);
+    C.mi = (float)(-1.0 / (double)m);
+    C.it = (int32_t)(0u - 0x400000u * mu);
+    C.il = (int32_t)(dig - 0x400000u * mu);
+    C.ip = (int32_t)(dig - 0x800000u * mu);
+    int8_t d[3];
+    i8_digits(((uint64_t)dig % m) * (uint64_t)radix, m, d);
+    C.c0 = d[0];
+    C.c1 = d[1];
+    C.c2 = d[2];
+    return C;
+}
+
+// Tables of the kernels in wave.hpp; w^e = P(e) for e < N.
+template <class PW>
+inline std::vector<int8_t> i8_wave_tables(int n, uint64_t m, uint64_t ninv, PW P, I8C* C) {
+    const int N = 1 << n;
+    std::vector<int8_t> t;
+    auto fw = [&](uint64_t e) -> uint64_t { return P(e & (N - 1)); };
+    auto bw = [&](uint64_t e) -> uint64_t { return P((0 - e) & (N - 1)); };
+    auto w16 = [&](int row, int in) { return fw((uint64_t)(N / 16) * row * in); };
+    auto v16 = [&](int row, int in) { return bw((uint64_t)(N / 16) * row * in); };
+    if (n <= 8) {
+        const int B = N / 16;
+        i8_matrix(t, m, [&](int row, int in) -> uint64_t {
+            return row / B != in / B ? 0 : fw((uint64_t)16 * (row % B) * (in % B));
+        });
+        i8_matrix(t, m, w16);
+        i8_matrix(t, m, v16);
+        i8_matrix(t, m, [&](int row, int in) -> uint64_t {
+            return row / B != in / B ? 0 : mulmod64(bw((uint64_t)16 * (row % B) * (in % B)), ninv, m);
+        });
+        for (int l = 0; l < 64; ++l)
+            for (int i = 0; i < 4; ++i) i8_pair(t, fw((uint64_t)(4 * (l >> 4) + i) * ((l & 15) % B)), m);
+        for (int l = 0; l < 64; ++l)
+            for (int i = 0; i < 4; ++i) i8_pair(t, bw((uint64_t)((4 * (l >> 4) + i) % B) * (l & 15)), m);
+        *C = make_i8c(m, B);
+        return t;
+    }
+    const int R1 = N / 256;
+    i8_matrix(t, m, w16);
+    i8_matrix(t, m, v16);
+    i8_matrix(t, m, [&](int row, int in) -> uint64_t {
+        return row / R1 != in / R1 ? 0 : mulmod64(bw((uint64_t)256 * (row % R1) * (in % R1)), ninv, m);
+    });
+    for (int u0 = 0; u0 < 16; ++u0)
+        i8_matrix(t, m, [&](int row, int in) -> uint64_t {
+            return row / R1 != in / R1 ? 0 : fw((uint64_t)256 * (row % R1) * (in % R1) + (uint64_t)16 * (in % R1) * u0);
+        });
+    for (int u0 = 0; u0 < 16; ++u0)
+        for (int l = 0; l < 64; ++l)
+            for (int i = 0; i < 4; ++i)
+                i8_pair(t, fw((uint64_t)(4 * (l >> 4) + i) * (u0 + 16 * ((l & 15) % R1))), m);
+    for (int l = 0; l < 64; ++l)
+        for (int i = 0; i < 4; ++i) i8_pair(t, bw((uint64_t)16 * ((4 * (l >> 4) + i) % R1) * (l & 15)), m);
+    for (int p0 = 0; p0 < 16; ++p0)
+        for (int l = 0; l < 64; ++l)
+            for (int i = 0; i < 4; ++i)
+                i8_pair(t, bw((uint64_t)p0 * ((l & 15) + 16 * ((4 * (l >> 4) + i) % R1))), m);
+    *C = make_i8c(m, 16);
+    return t;
+}
+
+}  // namespace nttmi

@@ -18,6 +18,27 @@ struct DevPlan {
     int logn, nmask;
 };
 
+// Constants of the matrix-core transforms of 32-bit words (i8dft.hpp) modulo m.
+struct I8C {
+    uint32_t m;
+    uint32_t small;      // m < 2^21: the tight residues take one more reduction
+    float k16, mg2, k8;  // -65536 / m; MAGIC (1 - k16); -256 / m
+    float mi;            // -1 / m
+    int32_t il, it;      // DIG - 0x400000 m; -0x400000 m (modulo 2^32)
+    int32_t ip;          // DIG - 0x800000 m
+    int32_t c0, c1, c2;  // digits of the first step's correction (I8Plan)
+};
+
+// Device tables of the matrix-core kernels for one plan (tab null: none for
+// this plan), in the order in which the lanes of a wave read them (i8plan.hpp).
+struct I8Plan {
+    const void* tab;
+    I8C C;
+};
+// 0.502 m + 2^20 < 2^23: tight residues fit the 24-bit products
+constexpr uint64_t I8_MAX_M = 14600000;
+constexpr int WAVE_MIN_LOG2N = 5, WAVE_MAX_LOG2N = 12;   // lengths of the wave kernels
+
 // Final store of the fused convolution as the two-prime combination: a1 holds
 // the item's residues mod m1 (same element offsets as h); the convolution runs
 // mod m2 = the plan's modulus; c = m1^-1 mod m2; h receives 64-bit words.
@@ -48,6 +69,10 @@ enum { SMALL_TILE_256 = 0, SMALL_TILE_WAVE = 1 };
 hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, void* h, const uint64_t* offs,
                              uint32_t count, const DevPlan& p, hipStream_t st, int tile = SMALL_TILE_256,
                              uint32_t* singular = nullptr);
+// The wave kernels (matrix cores): `count` convolutions of length 2^logn
+// (WAVE_MIN_LOG2N .. WAVE_MAX_LOG2N) of 32-bit words back to back.
+hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
+                            uint32_t cus, hipStream_t st);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
                             hipStream_t st, const void* y = nullptr);
 // scratch: items * 2N scratch words (conv), batch * N (ntt); scratch words are

@@ -1,0 +1,207 @@
+// Convolutions of 32-bit words of length 2^5 .. 2^12 on the matrix cores.
+//
+// A sequence is read as digits of its index, and a step contracts one digit
+// (i8dft.hpp).  In a wave's registers one digit (4 bits) lies in the lane group
+// and register element (g, i), one in the lane's column c, and the others name
+// registers and waves.  Sequences shorter than the digits allow fill up with the
+// sequence number s: the matrix is then block diagonal.
+#pragma once
+#include "i8dft.hpp"
+
+namespace nttmi {
+
+// A wave's buffer over `bytes` valid bytes (loads beyond read 0, stores beyond
+// are dropped).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buf(const void* p, uint32_t bytes) {
+    // (uniform by construction; said so, or the descriptor would be taken lane by lane)
+    const uint64_t a = (uint64_t)(uintptr_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), (short)0,
+                                             __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
+__device__ __forceinline__ int ld_raw(__amdgpu_buffer_rsrc_t b, uint32_t lane_word, uint32_t word) {
+    return (int)(__builtin_amdgcn_raw_buffer_load_b32(b, lane_word * 4, word * 4, 0) ^ DIG);
+}
+__device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uint32_t lane_word, uint32_t word) {
+    __builtin_amdgcn_raw_buffer_store_b32(x, b, lane_word * 4, word * 4, 0);
+}
+
+// ------------------------------------------------------------------ N <= 2^8
+// N = 16 B, B <= 16; a block of 256 consecutive elements (16 / B sequences) is
+// four registers of a wave, and a convolution never leaves the registers:
+// forward, t = t0 + 16 t', u = U + B u2: over (s, t') [c: t0 -> (s, U)], times
+// w^(t0 U), over t0; inverse, position p = p0 + B p', result v0 + 16 v1: over p'
+// [c: (s, p0) -> v0], times w^-(p0 v0), over (s, p0) with N^-1.
+constexpr int TINY_BLOCKS = 4;   // blocks per wave and pass (1024 elements)
+constexpr int TINY_ROUNDS = 4;   // passes per wave, at most
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_tiny(
+    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, int rounds, I8Plan p) {
+    constexpr int B = (1 << n) / 16;
+    const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
+    const I8K C(p.C);
+    const v4i* t = (const v4i*)p.tab;
+    const Mat A1 = ld_mat(t, lane), A2 = ld_mat(t + 192, lane), A3 = ld_mat(t + 384, lane), A4 = ld_mat(t + 576, lane);
+    const Tw T1 = ld_tw(t + 768, lane), T2 = ld_tw(t + 768 + 128, lane);
+    const Init ti = init_tight(C), raw = init_raw(ti, C, [&](int) { return (c & (B - 1)) == 0; });
+    const uint32_t lw = (uint32_t)(c + 64 * gr);
+    constexpr uint32_t CH = 256 * TINY_BLOCKS;
+    int nx[TINY_BLOCKS][4], ny[TINY_BLOCKS][4];   // the next blocks' words, loaded ahead
+    auto load = [&](const uint32_t* src, uint64_t at, int (&v)[TINY_BLOCKS][4]) {
+        const uint64_t a = at < words ? at : 0;
+        const auto bu = wave_buf(src + a, at < words ? (uint32_t)(words - a < CH ? words - a : CH) * 4 : 0u);
+#pragma unroll
+        for (int b = 0; b < TINY_BLOCKS; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                v[b][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(bu, lw * 4, (256 * b + 16 * i) * 4, 0);
+    };
+    // a workgroup's passes lie together
+    const uint64_t first = (uint64_t)blockIdx.x * (4 * CH) * rounds +
+                           (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * CH;
+    constexpr uint64_t step = 4 * CH;
+    load(f, first, nx);
+    load(g, first, ny);
+    for (int r = 0; r < rounds; ++r) {
+        const uint64_t at = first + r * step;
+        if (at >= words) break;
+        const auto bh = wave_buf(h + at, (uint32_t)(words - at < CH ? words - at : CH) * 4);
+        v4i x[TINY_BLOCKS], y[TINY_BLOCKS];
+#pragma unroll
+        for (int b = 0; b < TINY_BLOCKS; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x[b][i] = nx[b][i] ^ (int)DIG;
+                y[b][i] = ny[b][i] ^ (int)DIG;
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        if (r + 1 < rounds) {
+            load(f, at + step, nx);
+            load(g, at + step, ny);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < TINY_BLOCKS; ++b) {
+            x[b] = fold4_tw(digit_sums<TURN>(A1, x[b], raw), T1, C);
+            y[b] = fold4_tw(digit_sums<TURN>(A1, y[b], raw), T1, C);
+            x[b] = fold4_tight(digit_sums<KEEP>(A2, x[b], ti), C);
+            y[b] = fold4_tight(digit_sums<KEEP>(A2, y[b], ti), C);
+            x[b] = mul4_fg<SMALL>(x[b], y[b], C);
+            x[b] = fold4_tw(digit_sums<TURN>(A3, x[b], ti), T2, C);
+            x[b] = fold4_tight(digit_sums<KEEP>(A4, x[b], ti), C);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st_out(bh, out_word<SMALL>(x[b][i], C), lw, 256 * b + 16 * i);
+        }
+    }
+}
+
+// ------------------------------------------------------------------ 2^9 .. 2^12
+// N = 256 R1, R1 = 2 .. 16; a chunk of 4096 elements (16 / R1 sequences) in the
+// registers of the four waves of a workgroup, four registers each.
+// Forward, t = t0 + 16 p1 + 16 R1 p2, u = u0 + 16 u1 + 16 R1 u2:
+//   register (s, p1): over p2 (c: t0 stays), exchange (s, p1) against u0,
+//   register u0: over (s, p1), with w^(16 p1 u0) in the register's own matrix
+//   [c: t0 -> (s, u1)], times w^(t0 (u0 + 16 u1)), over t0 (c stays).
+// Inverse, position p0 + 16 p1 + 16 R1 p2, the same registers: register p0: over
+// p2 [c: (s, p1) -> v0], times w^-(16 p1 v0), over (s, p1) with N^-1 (c stays),
+// times w^-(p0 (v0 + 16 v1)), exchange p0 against (s, v1), register (s, v1):
+// over p0.  Loads and stores are rows of 16 consecutive words.
+// An exchange goes through LDS rows of 16 words, the words of one row the four
+// waves' four registers each: 16-byte accesses on both sides, the four pieces of
+// a row permuted by two bits of the column so that 16 rows touch every bank.
+// One chunk per workgroup, three workgroups per CU; its loads and those of its
+// matrices go out together.  Bound by vector issue (79 vector and 7 matrix
+// instructions per element).  2^26 elements, m = 13631489, against the LDS
+// kernel's fp64 butterflies: 2^12 341 -> 240 us, 2^9 290 -> 234 us; 2^18
+// elements 10.7 -> 6.9 and 9.0 -> 7.0 us.  Slower: one wave per chunk with the
+// transposes by lane-group swaps and no barrier (242 us, 73 against 59 us at
+// 2^24 elements: 8 waves per CU), persistent workgroups at two per CU (262 us).
+struct MidTab {   // 16-byte units, as in the plan's table
+    static constexpr int W = 0, V = 192, U = 384, M = 576, TF = M + 16 * 192, TK = TF + 16 * 128, TB = TK + 128;
+};
+__device__ __forceinline__ void mid_put(v4i* x, const v4i (&v)[4], int wave, int gr, int c) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        x[((4 * gr + i) * 16 + c) * 4 + (wave ^ (c >> 2))] = v4i{v[0][i], v[1][i], v[2][i], v[3][i]};
+}
+__device__ __forceinline__ void mid_get(const v4i* x, v4i (&v)[4], int wave, int gr, int c) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = x[((4 * wave + k) * 16 + c) * 4 + (gr ^ (c >> 2))];
+}
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_mid(
+    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, I8Plan p) {
+    constexpr int R1 = (1 << n) / 256, N = 1 << n;
+    using T = MidTab;
+    __shared__ v4i xch[3][1024];   // f, g, the inverse: two barriers
+    const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t at = (uint64_t)blockIdx.x * 4096;
+    const uint32_t bytes = (uint32_t)(words - at < 4096 ? words - at : 4096) * 4;
+    const auto bf = wave_buf(f + at, bytes), bg = wave_buf(g + at, bytes), bh = wave_buf(h + at, bytes);
+    const uint32_t lw = (uint32_t)(c + 16 * R1 * 4 * gr);
+    auto at_word = [&](int k, int i) {
+        return (uint32_t)(((4 * wave + k) / R1) * N + 16 * ((4 * wave + k) % R1) + 16 * R1 * i);
+    };
+    v4i x[4], y[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bf, lw, at_word(k, i));
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[k][i] = ld_raw(bg, lw, at_word(k, i));
+    const I8K C(p.C);
+    const v4i* t = (const v4i*)p.tab;
+    const Mat W = ld_mat(t + T::W, lane);
+    Mat M[4];
+    Tw tw[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        M[k] = ld_mat(t + T::M + (4 * wave + k) * 192, lane);
+        tw[k] = ld_tw(t + T::TF + (4 * wave + k) * 128, lane);
+    }
+    const Init lo = init_loose(C), ti = init_tight(C);
+    const Init raw = init_raw(lo, C, [&](int i) { return gr == 0 && i == 0; });
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = fold4_loose(digit_sums<KEEP>(W, x[k], raw), C);
+    mid_put(xch[0], x, wave, gr, c);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) y[k] = fold4_loose(digit_sums<KEEP>(W, y[k], raw), C);
+    mid_put(xch[1], y, wave, gr, c);
+    __syncthreads();
+    mid_get(xch[0], x, wave, gr, c);
+    mid_get(xch[1], y, wave, gr, c);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        x[k] = fold4_tw(digit_sums<TURN>(M[k], x[k], ti), tw[k], C);
+        y[k] = fold4_tw(digit_sums<TURN>(M[k], y[k], ti), tw[k], C);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tw[k] = ld_tw(t + T::TB + (4 * wave + k) * 128, lane);
+    const Mat V = ld_mat(t + T::V, lane), U = ld_mat(t + T::U, lane);
+    const Tw tk = ld_tw(t + T::TK, lane);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        x[k] = fold4_tight(digit_sums<KEEP>(W, x[k], ti), C);
+        y[k] = fold4_tight(digit_sums<KEEP>(W, y[k], ti), C);
+        x[k] = mul4_fg<SMALL>(x[k], y[k], C);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<TURN>(V, x[k], ti), tk, C);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<KEEP>(U, x[k], ti), tw[k], C);
+    mid_put(xch[2], x, wave, gr, c);
+    __syncthreads();
+    mid_get(xch[2], x, wave, gr, c);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        x[k] = fold4_tight(digit_sums<KEEP>(V, x[k], ti), C);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st_out(bh, out_word<SMALL>(x[k][i], C), lw, at_word(k, i));
+    }
+}
+
+}  // namespace nttmi

@@ -1,0 +1,86 @@
+"""GPU parity of the matrix-core convolutions (32-bit words, lengths 2^5 .. 2^12).
+
+The kernels carry residues as four signed bytes and take quotients from 32-bit
+floats, so the inputs sit where that arithmetic is tightest: words whose bytes
+are all at the ends of the signed range, residues at the ends of the centred
+range, and moduli at the ends of the range that the kernels take (primes
+k 2^13 + 1 either side of their limit of 14,600,000, above which the general
+kernels run, and either side of 2^21, below which a residue takes one more
+reduction, and tiny ones).  Item counts leave a part of the last chunk empty.
+The results are exact integers: equality (tolerance 0) with the oracle's direct
+sum for the first and the last item, and with the closed form h = N a b mod m
+for every item of constant operands."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+MODULI = [(13631489, 20), (14499841, 13), (14663681, 13), (2056193, 13), (2236417, 13), (12289, 12), (641, 7)]
+
+
+@pytest.fixture(scope="module")
+def nt():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    import paper_1005_1497_amd as nt
+    return nt
+
+
+def batch(nt, f, g, n, count, m):
+    order = nt.max_log2n(m)
+    desc = nt.BatchDesc(np.full(count, n), np.arange(count, dtype=np.int64) << n)
+    return host(nt.conv_batched(dev(f), dev(g), desc, m, root=nt.euler_root(m, order), root_log2order=order,
+                                flags=nt.FLAG_EULER))
+
+
+@pytest.mark.parametrize("m,top", MODULI)
+@pytest.mark.parametrize("n", range(5, 13))
+def test_lengths_and_moduli(nt, m, top, n):
+    if n > min(top, nt.max_log2n(m)):
+        pytest.skip("no transform of this length modulo m")
+    N = 1 << n
+    # one item; a chunk of 4096 elements and a part of the next
+    for count in (1, 4096 // N + 1):
+        rng = np.random.default_rng(1000 * n + count)
+        f = rng.integers(0, 1 << 32, size=count * N, dtype=np.uint64).astype(np.uint32)
+        g = rng.integers(0, 1 << 32, size=count * N, dtype=np.uint64).astype(np.uint32)
+        h = batch(nt, f, g, n, count, m)
+        for i in {0, count - 1}:
+            ref = oracle.conv_direct(f[i * N:(i + 1) * N] % m, g[i * N:(i + 1) * N] % m, m).astype(np.uint32)
+            assert np.array_equal(h[i * N:(i + 1) * N], ref), (count, i)
+        if count == 1:   # one convolution by itself
+            one = host(nt.conv_circular(dev(f), dev(g), m, flags=nt.FLAG_EULER))
+            assert np.array_equal(one, h)
+        for a, b in ((0x7F7F7F7F, 0x80808080), (0xFFFFFFFF, 0xFFFFFFFF), (m - 1, m - 1), ((m - 1) // 2, (m + 1) // 2)):
+            h = batch(nt, np.full(count * N, a, np.uint32), np.full(count * N, b, np.uint32), n, count, m)
+            assert np.all(h == N * a * b % m), (count, hex(a), hex(b))
+
+
+def test_capture_on_a_fresh_stream(nt):
+    """A batch of a short length is capturable on a stream that the library has
+    not seen, once the plan exists; replays follow the operands' new values."""
+    m, n, count = 13631489, 10, 9
+    rng = np.random.default_rng(7)
+    ops = [rng.integers(0, m, size=count << n).astype(np.uint32) for _ in range(4)]
+    want = [batch(nt, ops[0], ops[1], n, count, m), batch(nt, ops[2], ops[3], n, count, m)]
+    f, g = dev(ops[0]), dev(ops[1])
+    out = torch.empty_like(f)
+    order = nt.max_log2n(m)
+    desc = nt.BatchDesc(np.full(count, n), np.arange(count, dtype=np.int64) << n)
+    root = nt.euler_root(m, order)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        nt.conv_batched(f, g, desc, m, root=root, root_log2order=order, flags=nt.FLAG_EULER, out=out)
+    for k in (0, 1, 0):
+        f.copy_(dev(ops[2 * k]))
+        g.copy_(dev(ops[2 * k + 1]))
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host(out), want[k])
