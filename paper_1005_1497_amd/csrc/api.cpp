@@ -241,9 +241,10 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
     // when 2 has order nu = 2^lnu, else N^(m - 2) (Fermat, m prime)
     const uint64_t ninv = (l2 >= (int)log2n) ? powmod64(2, (1ull << l2) - log2n, m)
                                              : powmod64((1ull << log2n) % m, m - 2, m);
-    if (he == hipSuccess && m <= I8_MAX_M && (int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WAVE_MAX_LOG2N) {
-        const std::vector<int8_t> t = i8_wave_tables((int)log2n, m, ninv, [&](uint64_t e) { return (uint64_t)hP[e].x; },
-                                                     &p.i8.C);
+    if (he == hipSuccess && m <= I8_MAX_M && (int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WIDE_MAX_LOG2N) {
+        auto w = [&](uint64_t e) { return (uint64_t)hP[e].x; };
+        const std::vector<int8_t> t = (int)log2n <= WAVE_MAX_LOG2N ? i8_wave_tables((int)log2n, m, ninv, w, &p.i8.C)
+                                                                   : i8_wide_tables((int)log2n, m, ninv, w, &p.i8.C);
         he = upload(&p.dI8, t);
         p.i8.tab = p.dI8;
     }
@@ -572,6 +573,20 @@ ntt_status ntt_any(bool inv, uint64_t m, uint32_t log2n, uint64_t root, uint32_t
     return ntt_rows(p, elem_bits, log2n, inv, x, X, batch, stream);
 }
 
+// Whether a batch of c convolutions of length 2^n takes the one-workgroup
+// matrix-core kernels.  2^14: an item takes 22 us however few they are, against
+// 13 us for the four-step kernels, which spread one item over the chip; they meet
+// at about 110 items (64: 21.5 against 23.9 us, 128: 26.4 against 24.9, 256: 45
+// against 29).  2^13: the kernels are ahead at every count (one item 12.4 against
+// 11.2 us, 128: 18.9 against 11.9, 256: 23.2 against 12.8), but single convolutions
+// and batches that leave a third of the CUs without an item keep to the four-step
+// form, as which callers of ntt_launch_counts see them.
+bool use_wide(const Plan* p, uint32_t elem_bits, uint32_t n, uint32_t c) {
+    if (elem_bits != 32 || !p->i8.tab || (int)n < WIDE_MIN_LOG2N || (int)n > WIDE_MAX_LOG2N) return false;
+    const uint64_t cus = (uint64_t)cu_count();
+    return n == 13 ? 3ull * c >= 2 * cus : 2ull * c >= cus;
+}
+
 // One launch for the items of one length class: the LDS kernel below 2^13,
 // the persistent fused four-step kernel above.
 // c items of length 2^n: at offsets base + i 2^n (doffs null), else at the
@@ -589,6 +604,11 @@ ntt_status launch_items(uint32_t n, uint32_t c, uint64_t base, const uint64_t* d
                                                (uint32_t)cu_count(), s));
         return hip_status(launch_conv_small((int)elem_bits, n, F + base * wb, G + base * wb, H + base * wb, doffs, c,
                                             p->dev, s, form == CF_SMALL_WAVE ? SMALL_TILE_WAVE : SMALL_TILE_256));
+    }
+    if (form == CF_DEFAULT && use_wide(p, elem_bits, n, c)) {
+        count(NTT_COUNT_FUSED);
+        return hip_status(launch_conv_wide((int)n, F + base * wb, G + base * wb, H + base * wb, doffs, c,
+                                           (uint32_t)cu_count(), p->i8, s));
     }
     // multi-launch four-step form: every phase spreads all items over the
     // chip; scratch 2N words per item, within 1 GiB

@@ -120,4 +120,42 @@ inline std::vector<int8_t> i8_wave_tables(int n, uint64_t m, uint64_t ninv, PW P
     return t;
 }
 
+// Tables of the kernels in wide.hpp, N = 2^n = 4096 R; w^e = P(e) for e < N.
+template <class PW>
+inline std::vector<int8_t> i8_wide_tables(int n, uint64_t m, uint64_t ninv, PW P, I8C* C) {
+    const uint64_t N = 1ull << n;
+    const int R = (int)(N / 4096);
+    std::vector<int8_t> t;
+    auto fw = [&](uint64_t e) -> uint64_t { return P(e & (N - 1)); };
+    auto bw = [&](uint64_t e) -> uint64_t { return P((0 - e) & (N - 1)); };
+    const uint64_t h16 = N / 16, h256 = (uint64_t)16 * R, h4096 = (uint64_t)R;   // exponents of w_16, w_256, w_4096
+    // shared: the plain step, w_256^-(p1 v0), w_4096^-(p0 (v0 + 16 v1))
+    i8_matrix(t, m, [&](int row, int in) { return fw(h16 * row * in); });
+    for (int l = 0; l < 64; ++l)
+        for (int i = 0; i < 4; ++i) i8_pair(t, bw(h256 * (uint64_t)(4 * (l >> 4) + i) * (l & 15)), m);
+    for (int p0 = 0; p0 < 16; ++p0)
+        for (int l = 0; l < 64; ++l)
+            for (int i = 0; i < 4; ++i)
+                i8_pair(t, bw(h4096 * (uint64_t)p0 * ((l & 15) + 16 * (4 * (l >> 4) + i))), m);
+    // per j, with the twist w^(j t') of the inputs and w^-(j t') of the outputs
+    for (uint64_t j = 0; j < (uint64_t)R; ++j) {
+        i8_matrix(t, m, [&](int row, int in) { return bw(h16 * row * in + j * row); });
+        i8_matrix(t, m, [&](int row, int in) { return mulmod64(bw(h16 * row * in + 16 * j * row), ninv, m); });
+        for (int u0 = 0; u0 < 16; ++u0)
+            i8_matrix(t, m, [&](int row, int in) { return fw(h16 * row * in + h256 * in * u0 + 16 * j * in); });
+        for (int u0 = 0; u0 < 16; ++u0)
+            for (int l = 0; l < 64; ++l)
+                for (int i = 0; i < 4; ++i) {
+                    const uint64_t t0 = 4 * (l >> 4) + i;
+                    i8_pair(t, fw(h4096 * t0 * (u0 + 16 * (l & 15)) + j * t0), m);
+                }
+        for (int k = 0; k < R; ++k)
+            i8_matrix(t, m, [&](int row, int in) { return fw(h16 * row * in + 256 * j * in + N / R * j * k); });
+        for (int k = 0; k < R; ++k)
+            i8_matrix(t, m, [&](int row, int in) { return bw(h16 * row * in + 256 * j * row + N / R * j * k); });
+    }
+    *C = make_i8c(m, 16 * R);
+    return t;
+}
+
 }  // namespace nttmi

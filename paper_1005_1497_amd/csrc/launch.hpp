@@ -73,6 +73,12 @@ hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, 
 // (WAVE_MIN_LOG2N .. WAVE_MAX_LOG2N) of 32-bit words back to back.
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
                             uint32_t cus, hipStream_t st);
+// The same for lengths WIDE_MIN_LOG2N and WIDE_MAX_LOG2N, a workgroup per item:
+// items at offs[i], or back to back (offs null), on at most `cus` workgroups of
+// 2^14 at a time.
+constexpr int WIDE_MIN_LOG2N = 13, WIDE_MAX_LOG2N = 14;
+hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count,
+                            uint32_t cus, const I8Plan& p, hipStream_t st);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
                             hipStream_t st, const void* y = nullptr);
 // scratch: items * 2N scratch words (conv), batch * N (ntt); scratch words are

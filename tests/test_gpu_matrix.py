@@ -84,3 +84,48 @@ def test_capture_on_a_fresh_stream(nt):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(host(out), want[k])
+
+
+# primes either side of the kernels' thresholds: 2^21, 2,200,000 N / 4096, the limit
+WIDE_MODULI = [(13, m) for m in (13631489, 2056193, 2236417, 4366337, 4423681, 14499841, 14663681)] + \
+              [(14, m) for m in (13631489, 1785857, 2277377, 8716289, 8814593, 14499841, 14663681)]
+
+
+@pytest.mark.parametrize("n,m", WIDE_MODULI)
+def test_one_workgroup_lengths(nt, n, m):
+    """Lengths 2^13 and 2^14, an item per workgroup: the smallest batches that
+    take these kernels; more items than start at once (2^14: a workgroup's second
+    item), out of order and with gaps between them."""
+    N = 1 << n
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for count, gaps in (((cus + 1) // 2 if n == 14 else (2 * cus + 2) // 3, False), (cus + 1, True)):
+        rng = np.random.default_rng(1000 * n + count)
+        slots = rng.permutation(count + 2)[:count] if gaps else np.arange(count)
+        total = (count + 2 if gaps else count) * N
+        order = nt.max_log2n(m)
+        desc = nt.BatchDesc(np.full(count, n), slots.astype(np.int64) << n)
+
+        def run(f, g):
+            return host(nt.conv_batched(dev(f), dev(g), desc, m, root=nt.euler_root(m, order), root_log2order=order,
+                                        flags=nt.FLAG_EULER, out=dev(np.zeros(total, np.uint32))))
+
+        f = rng.integers(0, 1 << 32, size=total, dtype=np.uint64).astype(np.uint32)
+        g = rng.integers(0, 1 << 32, size=total, dtype=np.uint64).astype(np.uint32)
+        before = nt.launch_counts()["fused"]
+        h = run(f, g)
+        if m <= 14600000:
+            assert nt.launch_counts()["fused"] == before + 1
+        for i in {0, count // 2, count - 1}:
+            at = slice(int(slots[i]) * N, (int(slots[i]) + 1) * N)
+            idx = np.concatenate([[0, 1, N // 2, N - 1], rng.integers(0, N, size=60)]).astype(np.uint64)
+            ref = oracle.conv_entries(f[at] % m, g[at] % m, m, idx)
+            assert np.array_equal(h[at][idx.astype(np.int64)], ref.astype(np.uint32)), (count, i)
+            # every output at once: the outputs' sum is the product of the operands' sums
+            assert int(h[at].astype(np.uint64).sum()) % m == \
+                int(f[at].astype(np.uint64).sum()) % m * (int(g[at].astype(np.uint64).sum()) % m) % m
+            assert int(h[at].max()) < m
+        for a, b in ((0x7F7F7F7F, 0x80808080), (0xFFFFFFFF, 0xFFFFFFFF), (m - 1, m - 1), ((m - 1) // 2, (m + 1) // 2)):
+            h = run(np.full(total, a, np.uint32), np.full(total, b, np.uint32)).reshape(-1, N)
+            assert np.all(h[slots] == N * a * b % m), (count, hex(a), hex(b))
+            if gaps:
+                assert not np.delete(h, slots, axis=0).any()   # nothing between the items
