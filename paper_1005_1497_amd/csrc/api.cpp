@@ -243,10 +243,18 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
                                              : powmod64((1ull << log2n) % m, m - 2, m);
     if (he == hipSuccess && m <= I8_MAX_M && (int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WIDE_MAX_LOG2N) {
         auto w = [&](uint64_t e) { return (uint64_t)hP[e].x; };
-        const std::vector<int8_t> t = (int)log2n <= WAVE_MAX_LOG2N ? i8_wave_tables((int)log2n, m, ninv, w, &p.i8.C)
-                                                                   : i8_wide_tables((int)log2n, m, ninv, w, &p.i8.C);
+        const bool wave = (int)log2n <= WAVE_MAX_LOG2N;
+        std::vector<int8_t> t = wave ? i8_wave_tables((int)log2n, m, ninv, w, &p.i8.C)
+                                     : i8_wide_tables((int)log2n, m, ninv, w, &p.i8.C);
+        const size_t own = t.size();
+        if (wave) {
+            const std::vector<int8_t> fw = i8_wave_tables((int)log2n, m, 1, [&](uint64_t e) { return w((0 - e) & (N - 1)); },
+                                                          &p.i8.C);
+            t.insert(t.end(), fw.begin(), fw.end());
+        }
         he = upload(&p.dI8, t);
         p.i8.tab = p.dI8;
+        p.i8.fwd = p.dI8 + own;
     }
     if (he != hipSuccess) {
         if (p.dP) (void)hipFree(p.dP);
@@ -537,6 +545,8 @@ ntt_status ntt_rows(const Plan* p, uint32_t elem_bits, uint32_t log2n, bool inv,
                     uint32_t batch, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     count(NTT_COUNT_TRANSFORM);
+    if (elem_bits == 32 && p->i8.tab && (int)log2n <= WAVE_MAX_LOG2N)
+        return hip_status(launch_ntt_wave((int)log2n, inv, x, X, batch, p->i8, (uint32_t)cu_count(), s));
     if ((int)log2n <= SMALL_MAX_LOG2N)
         return hip_status(launch_ntt_small((int)elem_bits, log2n, inv, x, X, batch, p->dev, s));
     const size_t wb = elem_bits / 8;

@@ -33,6 +33,7 @@ struct I8C {
 // this plan), in the order in which the lanes of a wave read them (i8plan.hpp).
 struct I8Plan {
     const void* tab;
+    const void* fwd;   // up to 2^12: the same of the inverse root, without N^-1 (forward transforms)
     I8C C;
 };
 // 0.502 m + 2^20 < 2^23: tight residues fit the 24-bit products
@@ -73,6 +74,10 @@ hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, 
 // (WAVE_MIN_LOG2N .. WAVE_MAX_LOG2N) of 32-bit words back to back.
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
                             uint32_t cus, hipStream_t st);
+// Forward or inverse transforms of `batch` rows of length 2^logn (WAVE_MIN_LOG2N
+// .. WAVE_MAX_LOG2N) of 32-bit words back to back, natural order.
+hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& p, uint32_t cus,
+                           hipStream_t st);
 // The same for lengths WIDE_MIN_LOG2N and WIDE_MAX_LOG2N, a workgroup per item:
 // items at offs[i], or back to back (offs null), on at most `cus` workgroups of
 // 2^14 at a time.

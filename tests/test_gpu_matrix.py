@@ -129,3 +129,35 @@ def test_one_workgroup_lengths(nt, n, m):
             assert np.all(h[slots] == N * a * b % m), (count, hex(a), hex(b))
             if gaps:
                 assert not np.delete(h, slots, axis=0).any()   # nothing between the items
+
+
+@pytest.mark.parametrize("m,top", MODULI)
+@pytest.mark.parametrize("n", range(5, 13))
+def test_transforms(nt, m, top, n):
+    """Forward and inverse transforms, natural order: one row; a chunk of 4096
+    elements and a part of the next.  Every bin against the oracle's sum (the
+    inverse through its definition: N^-1 times the transform by w^-1), constants
+    and their spectra in closed form."""
+    if n > min(top, nt.max_log2n(m)):
+        pytest.skip("no transform of this length modulo m")
+    N = 1 << n
+    w = nt.euler_root(m, n)
+    bins = np.arange(N, dtype=np.uint64)
+    for rows in (1, 4096 // N + 1):
+        rng = np.random.default_rng(2000 * n + rows)
+        x = rng.integers(0, 1 << 32, size=(rows, N), dtype=np.uint64).astype(np.uint32)
+        X = host(nt.ntt_forward(dev(x), m, w, flags=nt.FLAG_EULER))
+        Y = host(nt.ntt_inverse(dev(x), m, w, flags=nt.FLAG_EULER))
+        some = sorted({0, rows - 1})
+        idx = np.tile(bins, (len(some), 1))
+        assert np.array_equal(X[some], oracle.ntt_bins_rows(x[some] % m, m, w, idx).astype(np.uint32))
+        inv = oracle.ntt_bins_rows(x[some] % m, m, pow(w, m - 2, m), idx).astype(np.uint64)
+        assert np.array_equal(Y[some], (inv * np.uint64(pow(N, m - 2, m)) % np.uint64(m)).astype(np.uint32))
+        assert np.array_equal(host(nt.ntt_inverse(dev(X), m, w, flags=nt.FLAG_EULER)), x % m)
+        for a in (0x7F7F7F7F, 0x80808080, 0xFFFFFFFF, m - 1, (m + 1) // 2):
+            for back in (False, True):
+                fn = nt.ntt_inverse if back else nt.ntt_forward
+                got = host(fn(dev(np.full((rows, N), a, np.uint32)), m, w, flags=nt.FLAG_EULER))
+                want = np.zeros((rows, N), np.uint32)
+                want[:, 0] = a % m if back else N * a % m
+                assert np.array_equal(got, want), (rows, hex(a), back)
