@@ -85,7 +85,7 @@ constexpr int WIDE_MIN_LOG2N = 13, WIDE_MAX_LOG2N = 14;
 hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count,
                             uint32_t cus, const I8Plan& p, hipStream_t st);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
-                            hipStream_t st, const void* y = nullptr);
+                            hipStream_t st);
 // scratch: items * 2N scratch words (conv), batch * N (ntt); scratch words are
 // wbits/8 bytes.  cus: the device's compute units (the workgroup size is
 // halved when 512-thread column blocks would not give each of them one).  tt:

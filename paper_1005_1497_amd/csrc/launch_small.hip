@@ -39,21 +39,18 @@ hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, 
 
 template <class W>
 static hipError_t ntt_small_t(int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
-                              hipStream_t st, const void* y) {
+                              hipStream_t st) {
     using T = typename W::word;
     switch (logn) {
 #define CASE(n)                                                                                                   \
     case n: {                                                                                                     \
         const uint32_t S = small_s(1 << n);                                                                       \
-        if (inv && y)                                                                                             \
-            hipLaunchKernelGGL((k_ntt_small<W, 1 << n, true, true>), dim3((batch + S - 1) / S), dim3(256), 0, st, \
-                               (const T*)x, (T*)X, batch, p, (const T*)y);                                        \
-        else if (inv)                                                                                             \
+        if (inv)                                                                                                  \
             hipLaunchKernelGGL((k_ntt_small<W, 1 << n, true>), dim3((batch + S - 1) / S), dim3(256), 0, st,       \
-                               (const T*)x, (T*)X, batch, p, nullptr);                                            \
+                               (const T*)x, (T*)X, batch, p);                                                     \
         else                                                                                                      \
             hipLaunchKernelGGL((k_ntt_small<W, 1 << n, false>), dim3((batch + S - 1) / S), dim3(256), 0, st,      \
-                               (const T*)x, (T*)X, batch, p, nullptr);                                            \
+                               (const T*)x, (T*)X, batch, p);                                                     \
         return hipGetLastError();                                                                                 \
     }
         NTT_SMALL_CASES(CASE)
@@ -64,11 +61,10 @@ static hipError_t ntt_small_t(int logn, bool inv, const void* x, void* X, uint32
 }
 
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
-                            hipStream_t st, const void* y) {
+                            hipStream_t st) {
     if (batch == 0) return hipSuccess;
-    if (y && !inv) return hipErrorInvalidValue;
-    return wbits == 32 ? ntt_small_t<W32>(logn, inv, x, X, batch, p, st, y)
-                       : ntt_small_t<W64>(logn, inv, x, X, batch, p, st, y);
+    return wbits == 32 ? ntt_small_t<W32>(logn, inv, x, X, batch, p, st)
+                       : ntt_small_t<W64>(logn, inv, x, X, batch, p, st);
 }
 
 }  // namespace nttmi
