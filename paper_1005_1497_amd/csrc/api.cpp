@@ -26,6 +26,8 @@ struct Plan {
     double* dTT = nullptr;
     uint32_t* dTT32 = nullptr;
     int8_t* dI8 = nullptr;   // tables of the matrix-core kernels
+    int8_t* dTrans = nullptr;
+    I8Plan trans[2] = {};    // 2^13 .. 2^19: the transforms', forward and inverse (tab null: none)
     I8Plan i8{};             // (tab null: no such kernel for this plan)
 };
 
@@ -256,7 +258,21 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
         p.i8.tab = p.dI8;
         p.i8.fwd = p.dI8 + own;
     }
+    if (he == hipSuccess && m <= I8_MAX_M && (int)log2n >= TRANS_MIN_LOG2N && (int)log2n <= TRANS_MAX_LOG2N) {
+        std::vector<int8_t> t;
+        size_t at[2];
+        for (int inv = 0; inv < 2; ++inv) {
+            const std::vector<int8_t> d = i8_trans_tables(
+                (int)log2n, m, inv ? ninv : 1, [&](uint64_t e) { return (uint64_t)hP[(inv ? 0 - e : e) & (N - 1)].x; },
+                &p.trans[inv].C);
+            at[inv] = t.size();
+            t.insert(t.end(), d.begin(), d.end());
+        }
+        he = upload(&p.dTrans, t);
+        for (int inv = 0; inv < 2; ++inv) p.trans[inv].tab = p.dTrans + at[inv];
+    }
     if (he != hipSuccess) {
+        if (p.dTrans) (void)hipFree(p.dTrans);
         if (p.dP) (void)hipFree(p.dP);
         if (p.dTT) (void)hipFree(p.dTT);
         if (p.dTT32) (void)hipFree(p.dTT32);
@@ -539,8 +555,8 @@ ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f
     return hip_status(launch_conv_fourstep((int)wbits, log2n, f, g, h, 1, 0, ws, p->dev, s, nullptr, (uint32_t)cu_count()));
 }
 
-// `batch` contiguous rows of N = 2^log2n, forward or inverse, plan built.  The
-// four-step path runs in chunks of rows whose scratch stays within 1 GiB.
+// `batch` contiguous rows of N = 2^log2n, forward or inverse, plan built.  Above
+// 2^12 they run in chunks of rows whose scratch stays within 1 GiB.
 ntt_status ntt_rows(const Plan* p, uint32_t elem_bits, uint32_t log2n, bool inv, const void* x, void* X,
                     uint32_t batch, void* stream) {
     hipStream_t s = (hipStream_t)stream;
@@ -551,14 +567,22 @@ ntt_status ntt_rows(const Plan* p, uint32_t elem_bits, uint32_t log2n, bool inv,
         return hip_status(launch_ntt_small((int)elem_bits, log2n, inv, x, X, batch, p->dev, s));
     const size_t wb = elem_bits / 8;
     const uint64_t per = (uint64_t)wb << log2n;
-    const uint32_t chunk = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, (1ull << 30) / per), 65535);
+    // (the matrix-core form keeps what one launch writes for the next within the
+    // memory-side cache: 2^26 elements of 2^16 in one chunk 280 us, 128 MiB of
+    // scratch 262, 64 MiB 273)
+    const bool trans = elem_bits == 32 && p->trans[inv].tab;
+    const uint64_t budget = trans ? 1ull << 27 : 1ull << 30;
+    const uint32_t chunk = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, budget / per), 65535);
     void* ws = nullptr;
     ntt_status st = get_buf(caches().work, stream, (size_t)(std::min(chunk, batch) * per), &ws);
     if (st != NTT_OK) return st;
     for (uint32_t r = 0; r < batch; r += chunk) {
         const uint32_t k = std::min(chunk, batch - r);
-        const hipError_t e = launch_ntt_fourstep((int)elem_bits, log2n, inv, (const char*)x + (size_t)r * per,
-                                                 (char*)X + (size_t)r * per, k, ws, p->dev, s, (uint32_t)cu_count());
+        const char* xr = (const char*)x + (size_t)r * per;
+        char* Xr = (char*)X + (size_t)r * per;
+        const hipError_t e = trans ? launch_ntt_trans((int)log2n, xr, Xr, k, ws, p->trans[inv], s)
+                                 : launch_ntt_fourstep((int)elem_bits, log2n, inv, xr, Xr, k, ws, p->dev, s,
+                                                       (uint32_t)cu_count());
         if (e != hipSuccess) return hip_status(e);
     }
     return NTT_OK;
@@ -1395,6 +1419,7 @@ void ntt_release_caches(void) {
         if (kv.second.dTT) (void)hipFree(kv.second.dTT);
         if (kv.second.dTT32) (void)hipFree(kv.second.dTT32);
         if (kv.second.dI8) (void)hipFree(kv.second.dI8);
+        if (kv.second.dTrans) (void)hipFree(kv.second.dTrans);
     }
     c.plans.clear();
     for (auto& kv : c.work) if (kv.second.ptr) (void)hipFree(kv.second.ptr);

@@ -176,6 +176,23 @@ __device__ __forceinline__ v4i fold4_tw(const Sums& s, const Tw& tw, const I8K& 
     }
     return r;
 }
+__device__ __forceinline__ v4i mul4_tw(const v4i& b, const Tw& tw, const I8K& C) {
+    v4i r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int w = tw.p[i >> 1][2 * (i & 1)], wq = tw.p[i >> 1][2 * (i & 1) + 1];
+        r[i] = (int)mul_tw_i(b[i], w, __builtin_bit_cast(float, wq), C);
+    }
+    return r;
+}
+// the same with the residues w alone (w / m formed here)
+__device__ __forceinline__ v4i fold4_w(const Sums& s, const v4i& w, const I8K& C) {
+    v4i r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        r[i] = (int)mul_tw_i(fold_tight(s.s0[i], s.s1[i], s.s2[i], C), w[i], (float)w[i] * C.vmi, C);
+    return r;
+}
 // F G as digits, of four tight residues each
 template <bool SMALL>
 __device__ __forceinline__ v4i mul4_fg(v4i F, v4i G, const I8K& C) {

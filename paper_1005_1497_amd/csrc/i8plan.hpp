@@ -120,6 +120,42 @@ inline std::vector<int8_t> i8_wave_tables(int n, uint64_t m, uint64_t ninv, PW P
     return t;
 }
 
+// Tables of the kernels in trans.hpp, N = 2^n = 256 Q; w^e = P(e) for e < N, the
+// transform's root (its inverse for the inverse), scale = 1 (N^-1).
+template <class PW>
+inline std::vector<int8_t> i8_trans_tables(int n, uint64_t m, uint64_t scale, PW P, I8C* C) {
+    const uint64_t N = 1ull << n, Q = N / 256, R = Q > 256 ? Q / 256 : 1, B = Q / R / 16;
+    auto fw = [&](uint64_t e) -> uint64_t { return P(e & (N - 1)); };
+    std::vector<int8_t> t;
+    // columns: w_256 = w^Q
+    i8_matrix(t, m, [&](int row, int in) { return fw(Q * 16 * row * in); });
+    for (int u0 = 0; u0 < 16; ++u0)
+        i8_matrix(t, m, [&](int row, int in) { return fw(Q * (16 * row * in + in * u0)); });
+    // rows, t1 = t0 + 16 p1 + 16 B k, u1 = j + R (U + B u2'): w_Q = w^256
+    i8_matrix(t, m, [&](int row, int in) { return mulmod64(fw(N / 16 * row * in), scale, m); });
+    for (uint64_t j = 0; j < R; ++j) {
+        for (uint64_t k = 0; k < R; ++k)
+            i8_matrix(t, m, [&](int row, int in) -> uint64_t {
+                const uint64_t p1 = in % B;
+                return row / B != in / B ? 0 : fw(256 * 16 * (R * (row % B) * p1 + j * (p1 + B * k)));
+            });
+        for (int l = 0; l < 64; ++l)
+            for (int i = 0; i < 4; ++i) i8_pair(t, fw((uint64_t)256 * (4 * (l >> 4) + i) * (j + R * ((l & 15) % B))), m);
+    }
+    // blocks of 16 columns t1; register u0; u2 = u0 + 16 (4 g + i): residues in (-m/2, m/2]
+    t.reserve(t.size() + 4 * N);
+    for (uint64_t r = 0; r < N / 256; ++r)
+        for (uint64_t l = 0; l < 64; ++l)
+            for (uint64_t i = 0; i < 4; ++i) {
+                const uint64_t w = fw((16 * (r / 16) + (l & 15)) * (r % 16 + 16 * (4 * (l >> 4) + i)));
+                const int32_t b = (int32_t)(2 * w > m ? (int64_t)w - (int64_t)m : (int64_t)w);
+                const int8_t* q = (const int8_t*)&b;
+                t.insert(t.end(), q, q + 4);
+            }
+    *C = make_i8c(m, 16);
+    return t;
+}
+
 // Tables of the kernels in wide.hpp, N = 2^n = 4096 R; w^e = P(e) for e < N.
 template <class PW>
 inline std::vector<int8_t> i8_wide_tables(int n, uint64_t m, uint64_t ninv, PW P, I8C* C) {

@@ -84,6 +84,12 @@ hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t 
 constexpr int WIDE_MIN_LOG2N = 13, WIDE_MAX_LOG2N = 14;
 hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count,
                             uint32_t cus, const I8Plan& p, hipStream_t st);
+// Transforms of `rows` rows of length 2^logn (TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N)
+// of 32-bit words back to back, the direction that of p's tables; scratch: rows * N
+// words.  x and X may be the same.
+constexpr int TRANS_MIN_LOG2N = 13, TRANS_MAX_LOG2N = 19;
+hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, void* scratch, const I8Plan& p,
+                            hipStream_t st);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
                             hipStream_t st);
 // scratch: items * 2N scratch words (conv), batch * N (ntt); scratch words are

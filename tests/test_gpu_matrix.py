@@ -161,3 +161,38 @@ def test_transforms(nt, m, top, n):
                 want = np.zeros((rows, N), np.uint32)
                 want[:, 0] = a % m if back else N * a % m
                 assert np.array_equal(got, want), (rows, hex(a), back)
+
+
+@pytest.mark.parametrize("m", [13631489, 1785857, 2277377, 14499841, 14663681, 7340033])
+@pytest.mark.parametrize("n", range(13, 20))
+def test_long_transforms(nt, n, m):
+    """Forward and inverse transforms of 2^13 .. 2^19, natural order: one row and
+    three (a last group of neighbouring workgroups that is not whole).  Chosen
+    bins against the oracle's sums, the inverse by its definition and by the round
+    trip of every word, constants and their spectra in closed form."""
+    if n > nt.max_log2n(m):
+        pytest.skip("no transform of this length modulo m")
+    N = 1 << n
+    w = nt.euler_root(m, n)
+    for rows in (1, 3):
+        rng = np.random.default_rng(3000 * n + rows)
+        x = rng.integers(0, 1 << 32, size=(rows, N), dtype=np.uint64).astype(np.uint32)
+        X = host(nt.ntt_forward(dev(x), m, w, flags=nt.FLAG_EULER))
+        Y = host(nt.ntt_inverse(dev(x), m, w, flags=nt.FLAG_EULER))
+        bins = np.concatenate([np.tile(np.array([0, 1, 255, 256, N // 2, N - 1], np.uint64), (rows, 1)),
+                               rng.integers(0, N, (rows, 24)).astype(np.uint64)], axis=1)
+        at = bins.astype(np.int64)
+        assert np.array_equal(np.take_along_axis(X, at, axis=1),
+                              oracle.ntt_bins_rows(x % m, m, w, bins).astype(np.uint32))
+        inv = oracle.ntt_bins_rows(x % m, m, pow(w, m - 2, m), bins).astype(np.uint64)
+        assert np.array_equal(np.take_along_axis(Y, at, axis=1),
+                              (inv * np.uint64(pow(N, m - 2, m)) % np.uint64(m)).astype(np.uint32))
+        assert np.array_equal(host(nt.ntt_inverse(dev(X), m, w, flags=nt.FLAG_EULER)), x % m)
+        assert np.array_equal(host(nt.ntt_forward(dev(Y), m, w, flags=nt.FLAG_EULER)), x % m)
+        for a in (0x7F7F7F7F, 0x80808080, 0xFFFFFFFF, m - 1, (m + 1) // 2):
+            for back in (False, True):
+                fn = nt.ntt_inverse if back else nt.ntt_forward
+                got = host(fn(dev(np.full((rows, N), a, np.uint32)), m, w, flags=nt.FLAG_EULER))
+                want = np.zeros((rows, N), np.uint32)
+                want[:, 0] = a % m if back else N * a % m
+                assert np.array_equal(got, want), (rows, hex(a), back)
