@@ -27,6 +27,8 @@ struct Plan {
     uint32_t* dTT32 = nullptr;
     int8_t* dI8 = nullptr;   // tables of the matrix-core kernels
     int8_t* dTrans = nullptr;
+    int8_t* dFour = nullptr;
+    I8Plan four{};           // and the rows of their convolutions
     I8Plan trans[2] = {};    // 2^13 .. 2^19: the transforms', forward and inverse (tab null: none)
     I8Plan i8{};             // (tab null: no such kernel for this plan)
 };
@@ -270,9 +272,17 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
         }
         he = upload(&p.dTrans, t);
         for (int inv = 0; inv < 2; ++inv) p.trans[inv].tab = p.dTrans + at[inv];
+        if (he == hipSuccess) {
+            size_t tti = 0;
+            he = upload(&p.dFour, i8_four_tables((int)log2n, m, ninv, [&](uint64_t e) { return (uint64_t)hP[e].x; }, &tti,
+                                                 &p.four.C));
+            p.four.tab = p.dFour;
+            p.four.tti = p.dFour + tti;
+        }
     }
     if (he != hipSuccess) {
         if (p.dTrans) (void)hipFree(p.dTrans);
+        if (p.dFour) (void)hipFree(p.dFour);
         if (p.dP) (void)hipFree(p.dP);
         if (p.dTT) (void)hipFree(p.dTT);
         if (p.dTT32) (void)hipFree(p.dTT32);
@@ -539,6 +549,29 @@ ntt_status check_range(uint32_t wbits, const void* x, uint64_t n, uint64_t m, vo
 }
 
 // One convolution of length 2^log2n (plan already built) on the stream.
+// Whether c convolutions of length 2^n, back to back, that take a multi-launch form
+// take the matrix-core one: up to 2^24 elements, where operands, results and scratch
+// lie in the memory-side cache (2^24 elements: 2^16 142 -> 134 us, 2^18 172 -> 157;
+// 2^21: 2^16 31.6 -> 25.9; one item of 2^19 21.2 -> 15.6, of 2^13 12.3 -> 11.5); beyond, its
+// launches wait for memory one after the other (2^25: 2^17 289 against 338 us, 2^18
+// 316 against 347), and it stays ahead at 2^19 alone (2^25 351 -> 328, 2^26 705 -> 661).
+bool use_four(const Plan* p, uint32_t elem_bits, uint32_t n, uint32_t c) {
+    return elem_bits == 32 && p->four.tab && (n >= 19 || ((uint64_t)c << n) <= (1u << 24));
+}
+// Scratch of a group of items: what leaves room for the operands in the memory-side
+// cache up to 2^24 elements (2^17: 64 MiB 145 us, 128 MiB 161), and beyond enough work
+// per launch (2^26 elements of 2^19: 698 and 661 us).
+ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const void* g, void* h, hipStream_t s,
+                     void* stream) {
+    const uint64_t per = 8ull << n, budget = ((uint64_t)c << n) <= (1u << 24) ? 1ull << 26 : 1ull << 27;
+    const uint32_t group = (uint32_t)std::min<uint64_t>(c, std::max<uint64_t>(1, budget / per));
+    void* ws = nullptr;
+    const ntt_status st = get_buf(caches().work, stream, (size_t)(group * per), &ws);
+    if (st != NTT_OK) return st;
+    count(NTT_COUNT_FOURSTEP);
+    return hip_status(launch_conv_four((int)n, f, g, h, c, group, ws, p->trans, p->four, s));
+}
+
 ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f, const void* g, void* h,
                     void* stream) {
     hipStream_t s = (hipStream_t)stream;
@@ -548,6 +581,7 @@ ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f
             return hip_status(launch_conv_wave((int)log2n, f, g, h, 1, p->i8, (uint32_t)cu_count(), s));
         return hip_status(launch_conv_small((int)wbits, log2n, f, g, h, nullptr, 1, p->dev, s));
     }
+    if (use_four(p, wbits, log2n, 1)) return conv_four(p, log2n, 1, f, g, h, s, stream);
     void* ws = nullptr;
     ntt_status st = get_buf(caches().work, stream, ((size_t)2 * (wbits / 8)) << log2n, &ws);
     if (st != NTT_OK) return st;
@@ -649,6 +683,8 @@ ntt_status launch_items(uint32_t n, uint32_t c, uint64_t base, const uint64_t* d
     const bool fourstep_ok = contiguous && (((uint64_t)2 * c * wb) << n) <= (1ull << 30);
     // (workgroup size: by the default rule, or as the form names it)
     auto fourstep = [&]() -> ntt_status {
+        if (form == CF_DEFAULT && use_four(p, elem_bits, n, c))
+            return conv_four(p, n, c, F + base * wb, G + base * wb, H + base * wb, s, stream);
         void* ws = nullptr;
         const ntt_status e = get_buf(caches().work, stream, (size_t)(((uint64_t)2 * c * wb) << n), &ws);
         if (e != NTT_OK) return e;
@@ -1017,6 +1053,8 @@ ntt_status conv_circular_noalloc(uint64_t m, uint32_t log2n, uint64_t root, uint
     const hipError_t e = noalloc_scratch(&ws);
     if (e != hipSuccess) return hip_status(e);
     count(NTT_COUNT_FOURSTEP);
+    if (use_four(p, elem_bits, log2n, 1))
+        return hip_status(launch_conv_four((int)log2n, f, g, h, 1, 1, ws, p->trans, p->four, s));
     return hip_status(launch_conv_fourstep((int)elem_bits, log2n, f, g, h, 1, 0, ws, p->dev, s, nullptr,
                                            (uint32_t)cu_count()));
 }
@@ -1420,6 +1458,7 @@ void ntt_release_caches(void) {
         if (kv.second.dTT32) (void)hipFree(kv.second.dTT32);
         if (kv.second.dI8) (void)hipFree(kv.second.dI8);
         if (kv.second.dTrans) (void)hipFree(kv.second.dTrans);
+        if (kv.second.dFour) (void)hipFree(kv.second.dFour);
     }
     c.plans.clear();
     for (auto& kv : c.work) if (kv.second.ptr) (void)hipFree(kv.second.ptr);

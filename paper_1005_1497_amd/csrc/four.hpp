@@ -1,0 +1,57 @@
+// Convolutions of 32-bit words of length 2^13 .. 2^19 on the matrix cores, in three
+// launches: N = 256 Q, element t = t1 + Q t2, frequency u = u2 + 256 u1.
+//   columns: length-256 transforms over t2 of f and g, times w^(t1 u2), into
+//     scratch rows of digits Y[u2 Q + t1];
+//   rows: the convolution of each pair of rows (the kernels of wave.hpp for
+//     length Q), times w^-(s1 u2), over the row of f;
+//   inverse columns: length-256 inverse transforms over u2, canonical store.
+// The frequency order stays inside, so nothing is transposed in memory.  Memory moves
+// 16, 12 and 8 bytes per element; the columns and the inverse columns are bound by
+// that (49 and 25 us per 2^24 elements), the rows by vector issue (47 us, 57 above 2^16).
+// m = 13631489, against the fp64 four-step kernels: one item of 2^13 12.3 -> 11.5 us, of
+// 2^16 13.1 -> 11.8, of 2^19 21.2 -> 15.6; 2^22 elements of 2^16 48 -> 38, of 2^19 61 -> 42;
+// 2^24 elements of 2^18 172 -> 151.  Slower: the phases of successive groups side by
+// side in one launch (2^24 elements of 2^16 162 us against 134; its columns then have
+// three waves per SIMD, not four), and workgroups of one die that keep an item's
+// scratch in its L2 and wait for each other between the phases (2^26 elements 660
+// against 610).
+#pragma once
+#include "trans.hpp"
+
+namespace nttmi {
+
+// Items back to back; scratch 2N words per item, rows of f and then of g.
+template <int n>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_four_cols(
+    const uint32_t* f, const uint32_t* g, uint32_t* Y, I8Plan p) {
+    constexpr uint32_t N = 1u << n, CH = N / 4096;
+    __shared__ v4i xch[1024];
+    const uint32_t id = pair_blocks(blockIdx.x, gridDim.x), half = id / CH;
+    cols_block<n, FORWARD, false>((half & 1 ? g : f) + (uint64_t)(half / 2) * N, Y + (uint64_t)half * N, id % CH, p, xch);
+}
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_four_inv(
+    const uint32_t* Y, uint32_t* h, I8Plan p) {
+    constexpr uint32_t N = 1u << n, CH = N / 4096;
+    __shared__ v4i xch[1024];
+    const uint32_t id = pair_blocks(blockIdx.x, gridDim.x), item = id / CH;
+    cols_block<n, INVERSE, SMALL>(Y + (uint64_t)item * 2 * N, h + (uint64_t)item * N, id % CH, p, xch);
+}
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_four_rows(uint32_t* Y, int rounds,
+                                                                                             I8Plan p) {
+    constexpr int la = n - 8;
+    constexpr uint32_t N = 1u << n, CH = N / 4096;
+    if constexpr (la <= 8) {
+        const uint32_t per = CH / rounds, item = blockIdx.x / per, bx = blockIdx.x % per;
+        uint32_t* y = Y + (uint64_t)item * 2 * N;
+        tiny_block<la, SMALL, true>(y, y + N, y, N, rounds, p, bx, (const v4i*)p.tti);
+    } else {
+        __shared__ v4i xch[3][1024];
+        const uint32_t item = blockIdx.x / CH, bx = blockIdx.x % CH;
+        uint32_t* y = Y + (uint64_t)item * 2 * N;
+        mid_block<la, SMALL, true>(y, y + N, y, N, p, bx, (const v4i*)p.tti, xch);
+    }
+}
+
+}  // namespace nttmi

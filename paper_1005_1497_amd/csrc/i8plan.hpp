@@ -156,6 +156,36 @@ inline std::vector<int8_t> i8_trans_tables(int n, uint64_t m, uint64_t scale, PW
     return t;
 }
 
+// Tables of the rows of four.hpp, N = 2^n = 256 Q: those of wave.hpp for length Q
+// (with the N^-1 of the whole) and, from `tti` on, the twiddles w^-(s1 u2) as residues
+// in (-m/2, m/2] in the order of the row kernels' registers.
+template <class PW>
+inline std::vector<int8_t> i8_four_tables(int n, uint64_t m, uint64_t ninv, PW P, size_t* tti, I8C* C) {
+    const int la = n - 8;
+    const uint64_t N = 1ull << n, A = 1ull << la;
+    std::vector<int8_t> t = i8_wave_tables(la, m, ninv, [&](uint64_t e) { return P(256 * e); }, C);
+    *tti = t.size();
+    t.reserve(t.size() + 4 * N);
+    for (uint64_t r = 0; r < N / 256; ++r)
+        for (uint64_t l = 0; l < 64; ++l)
+            for (uint64_t i = 0; i < 4; ++i) {
+                const uint64_t k = 4 * (l >> 4) + i, c = l & 15;
+                // the element's place in the scratch: blocks of 256 in order, or
+                // chunks of 4096 whose registers are (row, v1)
+                uint64_t e;
+                if (la <= 8) e = 256 * r + 16 * k + c;
+                else {
+                    const uint64_t R1 = A / 256, q = r % 16;
+                    e = 4096 * (r / 16) + (q / R1) * A + c + 16 * (q % R1) + 16 * R1 * k;
+                }
+                const uint64_t w = P((0 - (e & (A - 1)) * (e >> la)) & (N - 1));
+                const int32_t b = (int32_t)(2 * w > m ? (int64_t)w - (int64_t)m : (int64_t)w);
+                const int8_t* q = (const int8_t*)&b;
+                t.insert(t.end(), q, q + 4);
+            }
+    return t;
+}
+
 // Tables of the kernels in wide.hpp, N = 2^n = 4096 R; w^e = P(e) for e < N.
 template <class PW>
 inline std::vector<int8_t> i8_wide_tables(int n, uint64_t m, uint64_t ninv, PW P, I8C* C) {

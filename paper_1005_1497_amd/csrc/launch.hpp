@@ -34,6 +34,7 @@ struct I8C {
 struct I8Plan {
     const void* tab;
     const void* fwd;   // up to 2^12: the same of the inverse root, without N^-1 (forward transforms)
+    const void* tti;   // rows of longer convolutions: their twiddles
     I8C C;
 };
 // 0.502 m + 2^20 < 2^23: tight residues fit the 24-bit products
@@ -90,6 +91,12 @@ hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, con
 constexpr int TRANS_MIN_LOG2N = 13, TRANS_MAX_LOG2N = 19;
 hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, void* scratch, const I8Plan& p,
                             hipStream_t st);
+// Convolutions of lengths TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N of 32-bit words in three
+// launches per `group` items back to back.  trans: the transforms' plans of the length,
+// forward and inverse; rows: tables of the rows (tab) and twiddles (tti); scratch:
+// min(group, count) * 2N words.
+hipError_t launch_conv_four(int logn, const void* f, const void* g, void* h, uint32_t count, uint32_t group,
+                            void* scratch, const I8Plan* trans, const I8Plan& rows, hipStream_t st);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
                             hipStream_t st);
 // scratch: items * 2N scratch words (conv), batch * N (ntt); scratch words are

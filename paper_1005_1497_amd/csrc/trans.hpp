@@ -41,25 +41,27 @@ __device__ __forceinline__ uint32_t pair_blocks(uint32_t id, uint32_t blocks) {
 
 // Columns: 16 of them in the registers of four waves, t2 = p1 + 16 p2, u2 = u0 + 16 u1:
 // register p1 over p2, exchange p1 against u0, register u0 over p1 with w_256^(p1 u0)
-// in its matrix (the column stays in the lane).
-template <int n>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ntt_cols(const uint32_t* f,
-                                                                                            uint32_t* Y, I8Plan p) {
+// in its matrix (the column stays in the lane).  TRANSFORM: words to digits times
+// w^(t1 u2), the rows as above; FORWARD: the rows in their order; INVERSE: digits, the
+// rows in their order, to words.
+enum { TRANSFORM, FORWARD, INVERSE };
+template <int n, int KIND, bool SMALL>
+__device__ __forceinline__ void cols_block(const uint32_t* src, uint32_t* dst, uint32_t bx, const I8Plan& p,
+                                           v4i* xch) {
     using G = TransG<n>;
     using T = TransTab<n>;
-    constexpr uint32_t N = G::N, Q = G::Q, S = G::S, CH = N / 4096;
-    __shared__ v4i xch[1024];
+    constexpr uint32_t N = G::N, Q = G::Q, S = KIND == TRANSFORM ? G::S : 1;
     const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t id = pair_blocks(blockIdx.x, gridDim.x), bx = id % CH;
-    const uint64_t at = (uint64_t)(id / CH) * N;
-    const auto bf = wave_buf(f + at, N * 4), by = wave_buf(Y + at, N * 4);
+    const auto bs = wave_buf(src, N * 4), bd = wave_buf(dst, N * 4);
+    // row 4 wave + k + 16 (4 g + i)
+    const uint32_t lw = (uint32_t)c + 64 * Q * (uint32_t)gr;
+    auto at_word = [&](int k, int i) { return 16 * bx + Q * (uint32_t)(4 * wave + k + 16 * i); };
     v4i x[4], tt[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            x[k][i] = ld_raw(bf, (uint32_t)c + 64 * Q * (uint32_t)gr, 16 * bx + Q * (uint32_t)(4 * wave + k + 16 * i));
+        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bs, lw, at_word(k, i)) ^ (KIND == INVERSE ? (int)DIG : 0);
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat W = ld_mat(t + T::W, lane);
@@ -67,10 +69,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         M[k] = ld_mat(t + T::M + (4 * wave + k) * 192, lane);
-        tt[k] = t[T::TT + (bx * 16 + 4 * wave + k) * 64 + lane];
+        if constexpr (KIND != INVERSE) tt[k] = t[T::TT + (bx * 16 + 4 * wave + k) * 64 + lane];
     }
     const Init lo = init_loose(C), ti = init_tight(C);
-    const Init raw = init_raw(lo, C, [&](int i) { return gr == 0 && i == 0; });
+    const Init raw = KIND == INVERSE ? lo : init_raw(lo, C, [&](int i) { return gr == 0 && i == 0; });
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = fold4_loose(digit_sums<KEEP>(W, x[k], raw), C);
     mid_put(xch, x, wave, gr, c);
@@ -78,13 +80,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     mid_get(xch, x, wave, gr, c);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        x[k] = fold4_w(digit_sums<KEEP>(M[k], x[k], ti), tt[k], C);
+        const Sums s = digit_sums<KEEP>(M[k], x[k], ti);
+        x[k] = KIND == INVERSE ? fold4_tight(s, C) : fold4_w(s, tt[k], C);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t u1 = (uint32_t)(4 * gr + i);
-            st_out(by, (uint32_t)x[k][i], (u1 / S) * (16 * S * Q) + (u1 % S) * Q + (uint32_t)c, S * Q * (4 * wave + k) + 16 * bx);
+            if constexpr (KIND == TRANSFORM)
+                st_out(bd, (uint32_t)x[k][i], (u1 / S) * (16 * S * Q) + (u1 % S) * Q + (uint32_t)c,
+                       S * Q * (4 * wave + k) + 16 * bx);
+            else
+                st_out(bd, KIND == INVERSE ? out_word<SMALL>(x[k][i], C) : (uint32_t)x[k][i], lw, at_word(k, i));
         }
     }
+}
+
+template <int n>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ntt_cols(const uint32_t* f,
+                                                                                            uint32_t* Y, I8Plan p) {
+    constexpr uint32_t N = 1u << n, CH = N / 4096;
+    __shared__ v4i xch[1024];
+    const uint32_t id = pair_blocks(blockIdx.x, gridDim.x);
+    const uint64_t at = (uint64_t)(id / CH) * N;
+    cols_block<n, TRANSFORM, false>(f + at, Y + at, id % CH, p, xch);
 }
 
 // Rows: 4096 outputs, a chunk's for one j.

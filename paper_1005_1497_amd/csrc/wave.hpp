@@ -27,6 +27,11 @@ __device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uin
     __builtin_amdgcn_raw_buffer_store_b32(x, b, lane_word * 4, word * 4, 0);
 }
 
+// ROWS (of tiny_block and mid_block): the row phase of a longer transform
+// (four.hpp).  f and g are an item's rows of digits in scratch; the rows'
+// convolutions, times the twiddles rtt (four words per lane, in the order of the
+// registers), go to h as digits.
+
 // ------------------------------------------------------------------ N <= 2^8
 // N = 16 B, B <= 16; a block of 256 consecutive elements (16 / B sequences) is
 // four registers of a wave, and a convolution never leaves the registers:
@@ -35,16 +40,16 @@ __device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uin
 // [c: (s, p0) -> v0], times w^-(p0 v0), over (s, p0) with N^-1.
 constexpr int TINY_BLOCKS = 4;   // blocks per wave and pass (1024 elements)
 constexpr int TINY_ROUNDS = 4;   // passes per wave, at most
-template <int n, bool SMALL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_tiny(
-    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, int rounds, I8Plan p) {
+template <int n, bool SMALL, bool ROWS>
+__device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words,
+                                           int rounds, const I8Plan& p, uint32_t bx, const v4i* rtt) {
     constexpr int B = (1 << n) / 16;
     const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat A1 = ld_mat(t, lane), A2 = ld_mat(t + 192, lane), A3 = ld_mat(t + 384, lane), A4 = ld_mat(t + 576, lane);
     const Tw T1 = ld_tw(t + 768, lane), T2 = ld_tw(t + 768 + 128, lane);
-    const Init ti = init_tight(C), raw = init_raw(ti, C, [&](int) { return (c & (B - 1)) == 0; });
+    const Init ti = init_tight(C), raw = ROWS ? ti : init_raw(ti, C, [&](int) { return (c & (B - 1)) == 0; });
     const uint32_t lw = (uint32_t)(c + 64 * gr);
     constexpr uint32_t CH = 256 * TINY_BLOCKS;
     int nx[TINY_BLOCKS][4], ny[TINY_BLOCKS][4];   // the next blocks' words, loaded ahead
@@ -58,7 +63,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
                 v[b][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(bu, lw * 4, (256 * b + 16 * i) * 4, 0);
     };
     // a workgroup's passes lie together
-    const uint64_t first = (uint64_t)blockIdx.x * (4 * CH) * rounds +
+    const uint64_t first = (uint64_t)bx * (4 * CH) * rounds +
                            (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * CH;
     constexpr uint64_t step = 4 * CH;
     load(f, first, nx);
@@ -72,9 +77,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         for (int b = 0; b < TINY_BLOCKS; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                x[b][i] = nx[b][i] ^ (int)DIG;
-                y[b][i] = ny[b][i] ^ (int)DIG;
+                x[b][i] = nx[b][i] ^ (ROWS ? 0 : (int)DIG);
+                y[b][i] = ny[b][i] ^ (ROWS ? 0 : (int)DIG);
             }
+        v4i tt[TINY_BLOCKS];
+        if constexpr (ROWS) {
+#pragma unroll
+            for (int b = 0; b < TINY_BLOCKS; ++b) tt[b] = rtt[(at / 256 + b) * 64 + lane];
+        }
         __builtin_amdgcn_sched_barrier(0);
         if (r + 1 < rounds) {
             load(f, at + step, nx);
@@ -89,11 +99,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             y[b] = fold4_tight(digit_sums<KEEP>(A2, y[b], ti), C);
             x[b] = mul4_fg<SMALL>(x[b], y[b], C);
             x[b] = fold4_tw(digit_sums<TURN>(A3, x[b], ti), T2, C);
-            x[b] = fold4_tight(digit_sums<KEEP>(A4, x[b], ti), C);
+            const Sums s = digit_sums<KEEP>(A4, x[b], ti);
+            x[b] = ROWS ? fold4_w(s, tt[b], C) : fold4_tight(s, C);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) st_out(bh, out_word<SMALL>(x[b][i], C), lw, 256 * b + 16 * i);
+            for (int i = 0; i < 4; ++i)
+                st_out(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), lw, 256 * b + 16 * i);
         }
     }
+}
+
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_tiny(
+    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, int rounds, I8Plan p) {
+    tiny_block<n, SMALL, false>(f, g, h, words, rounds, p, blockIdx.x, nullptr);
 }
 
 // ------------------------------------------------------------------ 2^9 .. 2^12
@@ -129,15 +147,15 @@ __device__ __forceinline__ void mid_get(const v4i* x, v4i (&v)[4], int wave, int
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = x[((4 * wave + k) * 16 + c) * 4 + (gr ^ (c >> 2))];
 }
-template <int n, bool SMALL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_mid(
-    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, I8Plan p) {
+template <int n, bool SMALL, bool ROWS>
+__device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words,
+                                          const I8Plan& p, uint32_t bx, const v4i* rtt, v4i (*xch)[1024]) {
     constexpr int R1 = (1 << n) / 256, N = 1 << n;
     using T = MidTab;
-    __shared__ v4i xch[3][1024];   // f, g, the inverse: two barriers
+    // xch: f, g, the inverse: two barriers
     const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t at = (uint64_t)blockIdx.x * 4096;
+    const uint64_t at = (uint64_t)bx * 4096;
     const uint32_t bytes = (uint32_t)(words - at < 4096 ? words - at : 4096) * 4;
     const auto bf = wave_buf(f + at, bytes), bg = wave_buf(g + at, bytes), bh = wave_buf(h + at, bytes);
     const uint32_t lw = (uint32_t)(c + 16 * R1 * 4 * gr);
@@ -148,11 +166,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bf, lw, at_word(k, i));
+        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bf, lw, at_word(k, i)) ^ (ROWS ? (int)DIG : 0);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y[k][i] = ld_raw(bg, lw, at_word(k, i));
+        for (int i = 0; i < 4; ++i) y[k][i] = ld_raw(bg, lw, at_word(k, i)) ^ (ROWS ? (int)DIG : 0);
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat W = ld_mat(t + T::W, lane);
@@ -164,7 +182,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         tw[k] = ld_tw(t + T::TF + (4 * wave + k) * 128, lane);
     }
     const Init lo = init_loose(C), ti = init_tight(C);
-    const Init raw = init_raw(lo, C, [&](int i) { return gr == 0 && i == 0; });
+    const Init raw = ROWS ? lo : init_raw(lo, C, [&](int i) { return gr == 0 && i == 0; });
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = fold4_loose(digit_sums<KEEP>(W, x[k], raw), C);
     mid_put(xch[0], x, wave, gr, c);
@@ -194,14 +212,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<KEEP>(U, x[k], ti), tw[k], C);
     mid_put(xch[2], x, wave, gr, c);
+    v4i tt[4];
+    if constexpr (ROWS) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tt[k] = rtt[((uint64_t)bx * 16 + 4 * wave + k) * 64 + lane];
+    }
     __syncthreads();
     mid_get(xch[2], x, wave, gr, c);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        x[k] = fold4_tight(digit_sums<KEEP>(V, x[k], ti), C);
+        const Sums s = digit_sums<KEEP>(V, x[k], ti);
+        x[k] = ROWS ? fold4_w(s, tt[k], C) : fold4_tight(s, C);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) st_out(bh, out_word<SMALL>(x[k][i], C), lw, at_word(k, i));
+        for (int i = 0; i < 4; ++i) st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), lw, at_word(k, i));
     }
+}
+
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_mid(
+    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, I8Plan p) {
+    __shared__ v4i xch[3][1024];
+    mid_block<n, SMALL, false>(f, g, h, words, p, blockIdx.x, nullptr, xch);
 }
 
 // ------------------------------------------------------------------ transforms

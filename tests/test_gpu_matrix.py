@@ -196,3 +196,44 @@ def test_long_transforms(nt, n, m):
                 want = np.zeros((rows, N), np.uint32)
                 want[:, 0] = a % m if back else N * a % m
                 assert np.array_equal(got, want), (rows, hex(a), back)
+
+
+@pytest.mark.parametrize("m", [13631489, 1785857, 2277377, 14499841, 14663681, 7340033])
+@pytest.mark.parametrize("n", range(13, 20))
+def test_three_launch_lengths(nt, n, m):
+    """Convolutions of 2^13 .. 2^19 in three launches: one item and a small batch (a last
+    group of neighbouring workgroups that is not whole), each also over f.  Chosen
+    outputs against the oracle's sums, all of them through their sum, constants in
+    closed form."""
+    if n > nt.max_log2n(m):
+        pytest.skip("no transform of this length modulo m")
+    N = 1 << n
+    order = nt.max_log2n(m)
+    root = nt.euler_root(m, order)
+    for count in (1, 3):
+        rng = np.random.default_rng(4000 * n + count)
+        desc = nt.BatchDesc(np.full(count, n), np.arange(count, dtype=np.int64) << n)
+
+        def run(f, g, over=False):
+            if count == 1:
+                return host(nt.conv_circular(dev(f), dev(g), m, flags=nt.FLAG_EULER))
+            a = dev(f)
+            return host(nt.conv_batched(a, dev(g), desc, m, root=root, root_log2order=order, flags=nt.FLAG_EULER,
+                                        out=a if over else None))
+
+        f = rng.integers(0, 1 << 32, size=count * N, dtype=np.uint64).astype(np.uint32)
+        g = rng.integers(0, 1 << 32, size=count * N, dtype=np.uint64).astype(np.uint32)
+        before = nt.launch_counts()["fourstep"]
+        h = run(f, g)
+        assert nt.launch_counts()["fourstep"] == before + 1
+        assert np.array_equal(run(f, g, over=True), h)
+        for i in range(count):
+            at = slice(i * N, (i + 1) * N)
+            idx = np.concatenate([[0, 1, 255, 256, N // 2, N - 1], rng.integers(0, N, size=20)]).astype(np.uint64)
+            ref = oracle.conv_entries(f[at] % m, g[at] % m, m, idx)
+            assert np.array_equal(h[at][idx.astype(np.int64)], ref.astype(np.uint32)), (count, i)
+            assert int(h[at].astype(np.uint64).sum()) % m == \
+                int(f[at].astype(np.uint64).sum()) % m * (int(g[at].astype(np.uint64).sum()) % m) % m
+            assert int(h[at].max()) < m
+        for a, b in ((0x7F7F7F7F, 0x80808080), (0xFFFFFFFF, 0xFFFFFFFF), (m - 1, m - 1), ((m - 1) // 2, (m + 1) // 2)):
+            assert np.all(run(np.full(count * N, a, np.uint32), np.full(count * N, b, np.uint32)) == N * a * b % m)
