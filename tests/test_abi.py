@@ -241,3 +241,42 @@ def test_server_argument_validation(lib):
     assert lib.ntt_server_submit_staged(None, 1) == 1
     assert lib.ntt_server_stats(None, None, None, None, None, 0) == 1
     lib.ntt_server_destroy(None)
+
+
+def test_batch_descriptor_checks():
+    """conv_batched takes batches of one length whose items lie back to back in one
+    pass over the descriptor and others item by item: both refuse the same.  Every
+    call here is refused before any work (the last ones because h overlaps f in the
+    batch's last word), so no pointer is followed."""
+    import numpy as np
+    import paper_1005_1497_amd as nt
+    E_ARG, E_LENGTH = 1, 3
+
+    def status(log2n, offset, h=None, order=19):
+        n = np.asarray(log2n, np.uint8)
+        o = np.asarray(offset, np.uint64)
+        d = nt._BatchDesc(len(n), n.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8)),
+                          o.ctypes.data_as(ctypes.POINTER(ctypes.c_uint64)))
+        f = 1 << 40
+        return nt.lib.conv_batched(M, pow(2, 1 << (19 - order), M), order, 32, ctypes.byref(d), f, f,
+                                f + 4 if h is None else h, 0, None)
+
+    for cnt in (1, 2, 5, 64, 1001):
+        packed = [7 + 128 * i for i in range(cnt)]
+        last = packed[-1] + 128
+        f = 1 << 40
+        gap = packed[:-1] + [packed[-1] + 1]
+        for offs, end in ((packed, last), (gap, last + 1), (packed[::-1], last)):
+            assert status([7] * cnt, offs, h=f + 4 * (end - 1)) == E_ARG
+        for i in {0, cnt // 2, cnt - 1}:
+            n = [7] * cnt
+            n[i] = 21
+            assert status(n, packed) == E_LENGTH
+            n[i] = 8
+            if i + 1 < cnt:
+                assert status(n, packed) == E_ARG            # overlaps the next item
+        assert status([9] * cnt, [512 * i for i in range(cnt)], order=8) == E_LENGTH
+        limit = ((1 << 64) - 1 >> 3) - 128 * cnt
+        far = [limit + 1 + 128 * i for i in range(cnt)]      # the last item one past the limit
+        assert status([7] * cnt, far) == E_ARG
+        assert status([7] * cnt, [(1 << 64) - 128 + 128 * i & (1 << 64) - 1 for i in range(cnt)]) == E_ARG
