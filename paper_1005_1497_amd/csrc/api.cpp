@@ -562,14 +562,14 @@ bool use_four(const Plan* p, uint32_t elem_bits, uint32_t n, uint32_t c) {
 // cache up to 2^24 elements (2^17: 64 MiB 145 us, 128 MiB 161), and beyond enough work
 // per launch (2^26 elements of 2^19: 698 and 661 us).
 ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const void* g, void* h, hipStream_t s,
-                     void* stream) {
+                     void* stream, const Quotient* div = nullptr) {
     const uint64_t per = 8ull << n, budget = ((uint64_t)c << n) <= (1u << 24) ? 1ull << 26 : 1ull << 27;
     const uint32_t group = (uint32_t)std::min<uint64_t>(c, std::max<uint64_t>(1, budget / per));
     void* ws = nullptr;
     const ntt_status st = get_buf(caches().work, stream, (size_t)(group * per), &ws);
     if (st != NTT_OK) return st;
     count(NTT_COUNT_FOURSTEP);
-    return hip_status(launch_conv_four((int)n, f, g, h, c, group, ws, p->trans, p->four, s));
+    return hip_status(launch_conv_four((int)n, f, g, h, c, group, ws, p->trans, p->four, s, div));
 }
 
 ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f, const void* g, void* h,
@@ -1092,7 +1092,22 @@ ntt_status conv_deconvolve(uint64_t m, uint32_t log2n, uint64_t root, uint32_t e
     const char* F = (const char*)f;
     const char* Hh = (const char*)h;
     char* Gg = (char*)g;
-    if ((int)log2n <= SMALL_MAX_LOG2N) {
+    const Quotient div{p->dev.M, (uint32_t*)flag};
+    if (elem_bits == 32 && p->i8.tab && (int)log2n <= WAVE_MAX_LOG2N) {
+        count(NTT_COUNT_SMALL);
+        e = launch_conv_wave((int)log2n, F, Hh, Gg, batch, p->i8, (uint32_t)cu_count(), s, &div);
+    } else if (use_wide(p, elem_bits, log2n, batch)) {
+        count(NTT_COUNT_FUSED);
+        e = launch_conv_wide((int)log2n, F, Hh, Gg, nullptr, batch, (uint32_t)cu_count(), p->i8, s, &div);
+    } else if (elem_bits == 32 && p->four.tab &&
+               (((uint64_t)batch << log2n) <= (1u << 24) || 3ull * batch < 2ull * cu_count())) {
+        // the persistent kernel below leaves an item to one workgroup, and CUs without
+        // an item idle (100 of 2^18: 644 us, three launches 347; one of 2^19: 1373, 45; 400
+        // of 2^15 up to 2^24 elements even); with every CU busy it is ahead where the
+        // three launches wait for memory (1000 of 2^16: 638 against 722)
+        st = conv_four(p, log2n, batch, F, Hh, Gg, s, stream, &div);
+        if (st != NTT_OK) return st;
+    } else if ((int)log2n <= SMALL_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
         e = launch_conv_small((int)elem_bits, log2n, F, Hh, Gg, nullptr, batch, p->dev, s, SMALL_TILE_256,
                               (uint32_t*)flag);

@@ -37,21 +37,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const uint32_t id = pair_blocks(blockIdx.x, gridDim.x), item = id / CH;
     cols_block<n, INVERSE, SMALL>(Y + (uint64_t)item * 2 * N, h + (uint64_t)item * N, id % CH, p, xch);
 }
-template <int n, bool SMALL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_four_rows(uint32_t* Y, int rounds,
-                                                                                             I8Plan p) {
+template <int n, bool SMALL, class Point>
+__device__ __forceinline__ void four_rows(uint32_t* Y, int rounds, const I8Plan& p, const Point& point) {
     constexpr int la = n - 8;
     constexpr uint32_t N = 1u << n, CH = N / 4096;
     if constexpr (la <= 8) {
         const uint32_t per = CH / rounds, item = blockIdx.x / per, bx = blockIdx.x % per;
         uint32_t* y = Y + (uint64_t)item * 2 * N;
-        tiny_block<la, SMALL, true>(y, y + N, y, N, rounds, p, bx, (const v4i*)p.tti);
+        tiny_block<la, SMALL, true>(y, y + N, y, N, rounds, p, bx, (const v4i*)p.tti, point);
     } else {
         __shared__ v4i xch[3][1024];
         const uint32_t item = blockIdx.x / CH, bx = blockIdx.x % CH;
         uint32_t* y = Y + (uint64_t)item * 2 * N;
-        mid_block<la, SMALL, true>(y, y + N, y, N, p, bx, (const v4i*)p.tti, xch);
+        mid_block<la, SMALL, true>(y, y + N, y, N, p, bx, (const v4i*)p.tti, xch, point);
     }
+}
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_four_rows(uint32_t* Y, int rounds,
+                                                                                             I8Plan p) {
+    four_rows<n, SMALL>(Y, rounds, p, PointMul{});
+}
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_four_div(uint32_t* Y, int rounds,
+                                                                                            I8Plan p, Quotient q) {
+    four_rows<n, SMALL>(Y, rounds, p, PointDiv(q));
 }
 
 }  // namespace nttmi

@@ -37,6 +37,12 @@ struct I8Plan {
     const void* tti;   // rows of longer convolutions: their twiddles
     I8C C;
 };
+// The pointwise step of a deconvolution: the second operand's spectrum over the
+// first's; a zero coefficient of the first sets *singular.
+struct Quotient {
+    ModC M;
+    uint32_t* singular;
+};
 // 0.502 m + 2^20 < 2^23: tight residues fit the 24-bit products
 constexpr uint64_t I8_MAX_M = 14600000;
 constexpr int WAVE_MIN_LOG2N = 5, WAVE_MAX_LOG2N = 12;   // lengths of the wave kernels
@@ -73,8 +79,9 @@ hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, 
                              uint32_t* singular = nullptr);
 // The wave kernels (matrix cores): `count` convolutions of length 2^logn
 // (WAVE_MIN_LOG2N .. WAVE_MAX_LOG2N) of 32-bit words back to back.
+// div: the quotients g / f instead (exact deconvolutions).
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
-                            uint32_t cus, hipStream_t st);
+                            uint32_t cus, hipStream_t st, const Quotient* div = nullptr);
 // Forward or inverse transforms of `batch` rows of length 2^logn (WAVE_MIN_LOG2N
 // .. WAVE_MAX_LOG2N) of 32-bit words back to back, natural order.
 hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& p, uint32_t cus,
@@ -84,7 +91,7 @@ hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t 
 // 2^14 at a time.
 constexpr int WIDE_MIN_LOG2N = 13, WIDE_MAX_LOG2N = 14;
 hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count,
-                            uint32_t cus, const I8Plan& p, hipStream_t st);
+                            uint32_t cus, const I8Plan& p, hipStream_t st, const Quotient* div = nullptr);
 // Transforms of `rows` rows of length 2^logn (TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N)
 // of 32-bit words back to back, the direction that of p's tables; scratch: rows * N
 // words.  x and X may be the same.
@@ -96,7 +103,8 @@ hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, voi
 // forward and inverse; rows: tables of the rows (tab) and twiddles (tti); scratch:
 // min(group, count) * 2N words.
 hipError_t launch_conv_four(int logn, const void* f, const void* g, void* h, uint32_t count, uint32_t group,
-                            void* scratch, const I8Plan* trans, const I8Plan& rows, hipStream_t st);
+                            void* scratch, const I8Plan* trans, const I8Plan& rows, hipStream_t st,
+                            const Quotient* div = nullptr);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
                             hipStream_t st);
 // scratch: items * 2N scratch words (conv), batch * N (ntt); scratch words are

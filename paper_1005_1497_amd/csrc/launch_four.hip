@@ -7,7 +7,7 @@ namespace nttmi {
 
 template <int n, bool SMALL>
 static void four_t(const uint32_t* f, const uint32_t* g, uint32_t* h, uint32_t count, uint32_t group,
-                   uint32_t* Y, const I8Plan* trans, const I8Plan& rows, hipStream_t st) {
+                   uint32_t* Y, const I8Plan* trans, const I8Plan& rows, hipStream_t st, const Quotient* div) {
     constexpr uint32_t N = 1u << n, CH = N / 4096;
     for (uint32_t i = 0; i < count; i += group) {
         const uint32_t k = std::min(group, count - i);
@@ -15,13 +15,16 @@ static void four_t(const uint32_t* f, const uint32_t* g, uint32_t* h, uint32_t c
         hipLaunchKernelGGL((k_four_cols<n>), dim3(2 * k * CH), dim3(256), 0, st, f + at, g + at, Y, trans[0]);
         // two passes per workgroup where every CU has its three all the same
         const int rounds = n <= 16 && k * CH >= 768 * 2 ? 2 : 1;
-        hipLaunchKernelGGL((k_four_rows<n, SMALL>), dim3(k * CH / rounds), dim3(256), 0, st, Y, rounds, rows);
+        const dim3 grid(k * CH / rounds);
+        if (div) hipLaunchKernelGGL((k_four_div<n, SMALL>), grid, dim3(256), 0, st, Y, rounds, rows, *div);
+        else hipLaunchKernelGGL((k_four_rows<n, SMALL>), grid, dim3(256), 0, st, Y, rounds, rows);
         hipLaunchKernelGGL((k_four_inv<n, SMALL>), dim3(k * CH), dim3(256), 0, st, Y, h + at, trans[1]);
     }
 }
 
 hipError_t launch_conv_four(int logn, const void* f, const void* g, void* h, uint32_t count, uint32_t group,
-                            void* scratch, const I8Plan* trans, const I8Plan& rows, hipStream_t st) {
+                            void* scratch, const I8Plan* trans, const I8Plan& rows, hipStream_t st,
+                            const Quotient* div) {
     if (count == 0) return hipSuccess;
     if (group == 0) return hipErrorInvalidValue;
     switch (logn) {
@@ -29,10 +32,10 @@ hipError_t launch_conv_four(int logn, const void* f, const void* g, void* h, uin
     case n:                                                                                                         \
         if (rows.C.small)                                                                                           \
             four_t<n, true>((const uint32_t*)f, (const uint32_t*)g, (uint32_t*)h, count, group,                     \
-                            (uint32_t*)scratch, trans, rows, st);                                                   \
+                            (uint32_t*)scratch, trans, rows, st, div);                                                   \
         else                                                                                                        \
             four_t<n, false>((const uint32_t*)f, (const uint32_t*)g, (uint32_t*)h, count, group,                    \
-                             (uint32_t*)scratch, trans, rows, st);                                                  \
+                             (uint32_t*)scratch, trans, rows, st, div);                                                  \
         return hipGetLastError();
         CASE(13) CASE(14) CASE(15) CASE(16) CASE(17) CASE(18) CASE(19)
 #undef CASE

@@ -16,7 +16,7 @@ static int tiny_rounds(uint64_t words, uint32_t cus) {
 }
 
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
-                            uint32_t cus, hipStream_t st) {
+                            uint32_t cus, hipStream_t st, const Quotient* div) {
     if (count == 0) return hipSuccess;
     const uint64_t words = (uint64_t)count << logn;
     const uint32_t *ff = (const uint32_t*)f, *gg = (const uint32_t*)g;
@@ -24,18 +24,24 @@ hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uin
     const int rounds = tiny_rounds(words, cus);   // above 2^8: a workgroup per chunk
     const uint64_t share = 4ull * rounds * 256 * TINY_BLOCKS;
     const dim3 tiny((uint32_t)((words + share - 1) / share)), mid((uint32_t)((words + 4095) / 4096)), wg(256);
-    switch (logn) {
-#define TINY(n)                                                                                                    \
-    case n:                                                                                                        \
-        if (p.C.small) hipLaunchKernelGGL((k_conv_tiny<n, true>), tiny, wg, 0, st, ff, gg, hh, words, rounds, p);  \
-        else hipLaunchKernelGGL((k_conv_tiny<n, false>), tiny, wg, 0, st, ff, gg, hh, words, rounds, p);           \
+    switch (logn * 4 + (div ? 2 : 0) + (p.C.small ? 1 : 0)) {
+#define TINY(n, s)                                                                                          \
+    case n * 4 + s:                                                                                         \
+        hipLaunchKernelGGL((k_conv_tiny<n, s>), tiny, wg, 0, st, ff, gg, hh, words, rounds, p);             \
+        break;                                                                                              \
+    case n * 4 + 2 + s:                                                                                     \
+        hipLaunchKernelGGL((k_div_tiny<n, s>), tiny, wg, 0, st, ff, gg, hh, words, rounds, p, *div);        \
         break;
-#define MID(n)                                                                                                     \
-    case n:                                                                                                        \
-        if (p.C.small) hipLaunchKernelGGL((k_conv_mid<n, true>), mid, wg, 0, st, ff, gg, hh, words, p);            \
-        else hipLaunchKernelGGL((k_conv_mid<n, false>), mid, wg, 0, st, ff, gg, hh, words, p);                     \
+#define MID(n, s)                                                                                           \
+    case n * 4 + s:                                                                                         \
+        hipLaunchKernelGGL((k_conv_mid<n, s>), mid, wg, 0, st, ff, gg, hh, words, p);                       \
+        break;                                                                                              \
+    case n * 4 + 2 + s:                                                                                     \
+        hipLaunchKernelGGL((k_div_mid<n, s>), mid, wg, 0, st, ff, gg, hh, words, p, *div);                  \
         break;
-        TINY(5) TINY(6) TINY(7) TINY(8) MID(9) MID(10) MID(11) MID(12)
+#define BOTH(K, n) K(n, 0) K(n, 1)
+        BOTH(TINY, 5) BOTH(TINY, 6) BOTH(TINY, 7) BOTH(TINY, 8) BOTH(MID, 9) BOTH(MID, 10) BOTH(MID, 11) BOTH(MID, 12)
+#undef BOTH
 #undef TINY
 #undef MID
         default:

@@ -6,6 +6,7 @@
 // registers and waves.  Sequences shorter than the digits allow fill up with the
 // sequence number s: the matrix is then block diagonal.
 #pragma once
+#include "arith.hpp"
 #include "i8dft.hpp"
 
 namespace nttmi {
@@ -27,6 +28,48 @@ __device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uin
     __builtin_amdgcn_raw_buffer_store_b32(x, b, lane_word * 4, word * 4, 0);
 }
 
+// The pointwise steps over four registers of spectra (tight residues).
+// x <- x y, as digits:
+struct PointMul {   // (register by register, where the kernels form them)
+    static constexpr bool DIV = false;
+};
+// x <- y / x, as digits: the lane's sixteen divisors are inverted together
+// (Montgomery's simultaneous inversion): one Fermat power of their product, then each
+// inverse from the prefix products.  A zero divisor sets the flag and enters as 1.
+// In fp64: a product modulo m is four instructions there, and leaves no residue too
+// large for the next one.  (2^23 elements of 2^13: 92 -> 55 us.)
+struct PointDiv {
+    static constexpr bool DIV = true;
+    ModC M;
+    uint32_t* singular;
+    __device__ __forceinline__ explicit PointDiv(const Quotient& q) : M(q.M), singular(q.singular) {}
+    // valid: the registers (bits) that hold a sequence of the batch
+    __device__ __forceinline__ void operator()(v4i (&x)[4], const v4i (&y)[4], const I8K& C, uint32_t valid = 15) const {
+        double c[16];
+        bool zero = false;
+        auto divisor = [&](int i) {
+            const double r = reduce((double)x[i >> 2][i & 3], M);
+            zero |= r == 0.0 && ((valid >> (i >> 2)) & 1);
+            return r == 0.0 ? 1.0 : r;
+        };
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double r = divisor(i);
+            c[i] = i == 0 ? r : mulmod_var(c[i - 1], r, M);
+        }
+        if (zero) atomicOr(singular, 1u);
+        const uint32_t e = C.m - 2;
+        double inv = pow_mod<W32>(c[15], e, 31 - __builtin_clz(e), M);
+#pragma unroll
+        for (int i = 15; i >= 0; --i) {
+            const double ri = i == 0 ? inv : mulmod_var(inv, c[i - 1], M);
+            if (i > 0) inv = mulmod_var(inv, divisor(i), M);   // (formed again rather than kept)
+            const double q = mulmod_var(ri, (double)y[i >> 2][i & 3], M);
+            x[i >> 2][i & 3] = (int)(((uint32_t)(int32_t)q + DIG) ^ DIG);
+        }
+    }
+};
+
 // ROWS (of tiny_block and mid_block): the row phase of a longer transform
 // (four.hpp).  f and g are an item's rows of digits in scratch; the rows'
 // convolutions, times the twiddles rtt (four words per lane, in the order of the
@@ -40,9 +83,9 @@ __device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uin
 // [c: (s, p0) -> v0], times w^-(p0 v0), over (s, p0) with N^-1.
 constexpr int TINY_BLOCKS = 4;   // blocks per wave and pass (1024 elements)
 constexpr int TINY_ROUNDS = 4;   // passes per wave, at most
-template <int n, bool SMALL, bool ROWS>
+template <int n, bool SMALL, bool ROWS, class Point>
 __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words,
-                                           int rounds, const I8Plan& p, uint32_t bx, const v4i* rtt) {
+                                           int rounds, const I8Plan& p, uint32_t bx, const v4i* rtt, const Point& point) {
     constexpr int B = (1 << n) / 16;
     const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
     const I8K C(p.C);
@@ -91,13 +134,26 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
             load(g, at + step, ny);
         }
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int b = 0; b < TINY_BLOCKS; ++b) {
+        auto forward = [&](int b) {
             x[b] = fold4_tw(digit_sums<TURN>(A1, x[b], raw), T1, C);
             y[b] = fold4_tw(digit_sums<TURN>(A1, y[b], raw), T1, C);
             x[b] = fold4_tight(digit_sums<KEEP>(A2, x[b], ti), C);
             y[b] = fold4_tight(digit_sums<KEEP>(A2, y[b], ti), C);
-            x[b] = mul4_fg<SMALL>(x[b], y[b], C);
+        };
+        if constexpr (Point::DIV) {
+#pragma unroll
+            for (int b = 0; b < TINY_BLOCKS; ++b) forward(b);
+            uint32_t valid = 0;
+#pragma unroll
+            for (int b = 0; b < TINY_BLOCKS; ++b) valid |= (uint32_t)(at + 256 * b + (c / B) * 16 * B < words) << b;
+            point(x, y, C, valid);
+        }
+#pragma unroll
+        for (int b = 0; b < TINY_BLOCKS; ++b) {
+            if constexpr (!Point::DIV) {
+                forward(b);
+                x[b] = mul4_fg<SMALL>(x[b], y[b], C);
+            }
             x[b] = fold4_tw(digit_sums<TURN>(A3, x[b], ti), T2, C);
             const Sums s = digit_sums<KEEP>(A4, x[b], ti);
             x[b] = ROWS ? fold4_w(s, tt[b], C) : fold4_tight(s, C);
@@ -111,7 +167,12 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
 template <int n, bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_tiny(
     const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, int rounds, I8Plan p) {
-    tiny_block<n, SMALL, false>(f, g, h, words, rounds, p, blockIdx.x, nullptr);
+    tiny_block<n, SMALL, false>(f, g, h, words, rounds, p, blockIdx.x, nullptr, PointMul{});
+}
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_div_tiny(
+    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, int rounds, I8Plan p, Quotient q) {
+    tiny_block<n, SMALL, false>(f, g, h, words, rounds, p, blockIdx.x, nullptr, PointDiv(q));
 }
 
 // ------------------------------------------------------------------ 2^9 .. 2^12
@@ -147,9 +208,9 @@ __device__ __forceinline__ void mid_get(const v4i* x, v4i (&v)[4], int wave, int
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = x[((4 * wave + k) * 16 + c) * 4 + (gr ^ (c >> 2))];
 }
-template <int n, bool SMALL, bool ROWS>
+template <int n, bool SMALL, bool ROWS, class Point>
 __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words,
-                                          const I8Plan& p, uint32_t bx, const v4i* rtt, v4i (*xch)[1024]) {
+                                          const I8Plan& p, uint32_t bx, const v4i* rtt, v4i (*xch)[1024], const Point& point) {
     constexpr int R1 = (1 << n) / 256, N = 1 << n;
     using T = MidTab;
     // xch: f, g, the inverse: two barriers
@@ -205,8 +266,9 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
     for (int k = 0; k < 4; ++k) {
         x[k] = fold4_tight(digit_sums<KEEP>(W, x[k], ti), C);
         y[k] = fold4_tight(digit_sums<KEEP>(W, y[k], ti), C);
-        x[k] = mul4_fg<SMALL>(x[k], y[k], C);
+        if constexpr (!Point::DIV) x[k] = mul4_fg<SMALL>(x[k], y[k], C);
     }
+    if constexpr (Point::DIV) point(x, y, C, at + (c / R1) * N < words ? 15 : 0);
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<TURN>(V, x[k], ti), tk, C);
 #pragma unroll
@@ -232,7 +294,13 @@ template <int n, bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_mid(
     const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, I8Plan p) {
     __shared__ v4i xch[3][1024];
-    mid_block<n, SMALL, false>(f, g, h, words, p, blockIdx.x, nullptr, xch);
+    mid_block<n, SMALL, false>(f, g, h, words, p, blockIdx.x, nullptr, xch, PointMul{});
+}
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_div_mid(
+    const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, I8Plan p, Quotient q) {
+    __shared__ v4i xch[3][1024];
+    mid_block<n, SMALL, false>(f, g, h, words, p, blockIdx.x, nullptr, xch, PointDiv(q));
 }
 
 // ------------------------------------------------------------------ transforms

@@ -79,9 +79,9 @@ __device__ __forceinline__ void ld_m(WideM& m, const v4i* tj, int w4, int lane) 
     }
 }
 // Transform j between the exchanges: x, y (registers 4 w4 + k: u0) -> x (registers p0).
-template <bool SMALL>
+template <bool SMALL, class Point>
 __device__ __forceinline__ void wide_core(v4i (&x)[4], v4i (&y)[4], const WideM& m, const v4i* ts, const v4i* tj, int w4,
-                                         int lane, const I8K& C) {
+                                         int lane, const I8K& C, const Point& point) {
     using T = WideTab;
     const Init ti = init_tight(C);
     const Mat W = ld_mat(ts + T::W, lane), V = ld_mat(tj + T::V1, lane);
@@ -99,8 +99,9 @@ __device__ __forceinline__ void wide_core(v4i (&x)[4], v4i (&y)[4], const WideM&
     for (int k = 0; k < 4; ++k) {
         x[k] = fold4_tight(digit_sums<KEEP>(W, x[k], ti), C);
         y[k] = fold4_tight(digit_sums<KEEP>(W, y[k], ti), C);
-        x[k] = mul4_fg<SMALL>(x[k], y[k], C);
+        if constexpr (!Point::DIV) x[k] = mul4_fg<SMALL>(x[k], y[k], C);
     }
+    if constexpr (Point::DIV) point(x, y, C);
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<TURN>(V, x[k], ti), tk, C);
 #pragma unroll
@@ -108,9 +109,9 @@ __device__ __forceinline__ void wide_core(v4i (&x)[4], v4i (&y)[4], const WideM&
 }
 
 // MODE 0: no extra reductions, 1: of the results (m < R 2.2e6), 2: also before the products (small moduli)
-template <int n, int MODE>
-__global__ __launch_bounds__(64 * WideG<n>::WAVES) __attribute__((amdgpu_waves_per_eu(n == 13 ? 3 : 2, n == 13 ? 3 : 2))) void
-k_conv_wide(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* __restrict__ offs, uint32_t count, I8Plan p) {
+template <int n, int MODE, class Point>
+__device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* offs,
+                                           uint32_t count, I8Plan p, const Point& point) {
     using G = WideG<n>;
     using T = WideTab;
     constexpr int R = G::R, PW = G::PW;
@@ -204,7 +205,7 @@ k_conv_wide(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* _
         __syncthreads();
         mid_get(xch[0], x, wave, gr, c);
         mid_get(xch[2], y, wave, gr, c);
-        wide_core<SMALL>(x, y, m, ts, tab(0), w4, lane, C);
+        wide_core<SMALL>(x, y, m, ts, tab(0), w4, lane, C, point);
         v4i z[4];
         mid_get(xch[1], z, wave, gr, c);
         __syncthreads();
@@ -213,7 +214,7 @@ k_conv_wide(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* _
         ld_m(m, tab(1), w4, lane);
         __syncthreads();
         mid_get(xch[0], y, wave, gr, c);
-        wide_core<SMALL>(z, y, m, ts, tab(1), w4, lane, C);
+        wide_core<SMALL>(z, y, m, ts, tab(1), w4, lane, C, point);
         mid_put(xch[1], z, wave, gr, c);
         __syncthreads();
         mid_get(xch[2], x, wave, gr, c);
@@ -251,13 +252,13 @@ k_conv_wide(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* _
             v4i x[4], y[4];
             wide_get<4>(xch[group], x, w4, gr, c);
             wide_get<4>(xch[4 + group], y, w4, gr, c);
-            wide_core<SMALL>(x, y, m, ts, tab(group), w4, lane, C);
+            wide_core<SMALL>(x, y, m, ts, tab(group), w4, lane, C, point);
             wide_put<4>(xch[8 + group], x, w4, gr, c);
             ld_m(m, tab(2 + group), w4, lane);
             wide_get<4>(xch[2 + group], x, w4, gr, c);
             wide_get<4>(xch[6 + group], y, w4, gr, c);
             __syncthreads();   // xch[group] is read
-            wide_core<SMALL>(x, y, m, ts, tab(2 + group), w4, lane, C);
+            wide_core<SMALL>(x, y, m, ts, tab(2 + group), w4, lane, C, point);
             wide_put<4>(xch[group], x, w4, gr, c);
             Mat L[R];
             mats(L, T::L(R), T::size(R));
@@ -276,6 +277,18 @@ k_conv_wide(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* _
             last(a, item, L);
         }
     }
+}
+
+template <int n, int MODE>
+__global__ __launch_bounds__(64 * WideG<n>::WAVES) __attribute__((amdgpu_waves_per_eu(n == 13 ? 3 : 2, n == 13 ? 3 : 2))) void
+k_conv_wide(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* __restrict__ offs, uint32_t count, I8Plan p) {
+    wide_block<n, MODE>(f, g, h, offs, count, p, PointMul{});
+}
+template <int n, int MODE>
+__global__ __launch_bounds__(64 * WideG<n>::WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_div_wide(
+    const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* __restrict__ offs, uint32_t count, I8Plan p,
+    Quotient q) {
+    wide_block<n, MODE>(f, g, h, offs, count, p, PointDiv(q));
 }
 
 }  // namespace nttmi

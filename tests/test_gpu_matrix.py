@@ -237,3 +237,33 @@ def test_three_launch_lengths(nt, n, m):
             assert int(h[at].max()) < m
         for a, b in ((0x7F7F7F7F, 0x80808080), (0xFFFFFFFF, 0xFFFFFFFF), (m - 1, m - 1), ((m - 1) // 2, (m + 1) // 2)):
             assert np.all(run(np.full(count * N, a, np.uint32), np.full(count * N, b, np.uint32)) == N * a * b % m)
+
+
+@pytest.mark.parametrize("m", [13631489, 2056193, 2236417, 14499841, 14663681, 12289])
+@pytest.mark.parametrize("n", range(5, 18))
+def test_quotients(nt, n, m):
+    """Deconvolutions through each of the matrix-core forms: one row, a part of a chunk,
+    and as many rows as the one-workgroup kernels take.  g from f and f * g exactly,
+    with divisors whose spectra (one of them all ones but one) have no zero; a zero
+    coefficient in the last row alone is reported."""
+    if n > min(nt.max_log2n(m), 20):
+        pytest.skip("no transform of this length modulo m")
+    N = 1 << n
+    w = nt.euler_root(m, n)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for rows in {1, max(3, 4096 // N + 1), cus if n in (13, 14) else 2}:
+        rng = np.random.default_rng(5000 * n + rows)
+        F = rng.integers(1, m, size=(rows, N)).astype(np.uint32)
+        F[0] = 1
+        F[0, N - 1] = m - 1
+        f = nt.ntt_inverse(dev(F), m, w, flags=nt.FLAG_EULER)
+        g = rng.integers(0, m, size=(rows, N)).astype(np.uint32)
+        g[-1] = m - 1
+        G = host(nt.ntt_forward(dev(g), m, w, flags=nt.FLAG_EULER)).astype(np.uint64)
+        h = nt.ntt_inverse(dev((G * F % np.uint64(m)).astype(np.uint32)), m, w, flags=nt.FLAG_EULER)
+        assert np.array_equal(host(nt.deconvolve(f, h, m, w, flags=nt.FLAG_EULER)), g), rows
+        F[-1, N // 2] = 0
+        f0 = nt.ntt_inverse(dev(F), m, w, flags=nt.FLAG_EULER)
+        with pytest.raises(nt.NttError) as e:
+            nt.deconvolve(f0, h, m, w, flags=nt.FLAG_EULER)
+        assert e.value.name == "NTT_E_SINGULAR"
