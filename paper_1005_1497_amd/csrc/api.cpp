@@ -1159,22 +1159,25 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     st = get_plan(m1, log2n, r1, l1, &p1);
     if (st == NTT_OK) st = get_plan(m2, log2n, r2, l2, &p2);
     if (st != NTT_OK) return st;
-    // residues mod m1, then the convolution mod m2 whose final store combines
-    // both (the fused kernel's CRT store above 2^12; a combine kernel below)
+    // residues mod m1, then the convolution mod m2; a pass that combines both, or
+    // the persistent kernel's store that does
     void* tmp = nullptr;
     st = get_buf(caches().tune, stream, 2 * in_bytes, &tmp);
     if (st != NTT_OK) return st;
     uint32_t* a1 = (uint32_t*)tmp;
     uint32_t* a2 = a1 + (size_t)batch * N;
-    std::vector<uint64_t> off(batch);
-    for (uint32_t i = 0; i < batch; ++i) off[i] = (uint64_t)i * N;
     hipStream_t s = (hipStream_t)stream;
     const uint32_t c = (uint32_t)powmod64(m1 % m2, m2 - 2, m2);   // m1^-1 mod m2
-    st = launch_class(log2n, off, p1, 32, (const char*)f, (const char*)g, (char*)a1, s, stream);
+    st = launch_items(log2n, batch, 0, nullptr, p1, 32, (const char*)f, (const char*)g, (char*)a1, s, stream, CF_DEFAULT);
     if (st != NTT_OK) return st;
-    if ((int)log2n > SMALL_MAX_LOG2N) {
+    // The persistent kernel's combining store saves a pass over both residues, but
+    // leaves an item to one workgroup: it is for lengths from 2^14 on with every CU busy
+    // (us, two convolutions and a combining pass / persistent: 1000 of 2^13 90 / 130,
+    // 8192 717 / 791; 800 of 2^14 221 / 236, 4096 945 / 914; 200 of 2^15 130 / 149, 400
+    // 282 / 268; 128 of 2^17 377 / 470, 256 663 / 634; one of 2^19 34 / 1297)
+    uint64_t grid = log2n < 14 ? 0 : (uint64_t)std::max(1, cu_count()) * std::max(1, fused_blocks_per_cu(32, (int)log2n));
+    if (log2n == 14 ? batch > 1024 : log2n > 14 && 3ull * batch >= 2 * grid) {
         const uint64_t per_wg = (uint64_t)2 * 4 << log2n;
-        uint64_t grid = (uint64_t)std::max(1, cu_count()) * std::max(1, fused_blocks_per_cu(32, (int)log2n));
         grid = std::min<uint64_t>(grid, std::max<uint64_t>(1, (1ull << 30) / per_wg));
         grid = std::min<uint64_t>(grid, batch);
         void* ws = nullptr;
@@ -1188,7 +1191,7 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
         return hip_status(launch_conv_fused(32, (int)log2n, f, g, nullptr, nullptr, batch, ws, q, (uint32_t)grid,
                                             p2->dev, s, nullptr, &cs));
     }
-    st = launch_class(log2n, off, p2, 32, (const char*)f, (const char*)g, (char*)a2, s, stream);
+    st = launch_items(log2n, batch, 0, nullptr, p2, 32, (const char*)f, (const char*)g, (char*)a2, s, stream, CF_DEFAULT);
     if (st != NTT_OK) return st;
     return hip_status(launch_crt_combine(a1, a2, (uint64_t*)h, (uint64_t)batch * N, (uint32_t)m1, (uint32_t)m2, c, s));
 }

@@ -267,3 +267,24 @@ def test_quotients(nt, n, m):
         with pytest.raises(nt.NttError) as e:
             nt.deconvolve(f0, h, m, w, flags=nt.FLAG_EULER)
         assert e.value.name == "NTT_E_SINGULAR"
+
+
+@pytest.mark.parametrize("n", [13, 14, 15, 16, 17])
+def test_crt_either_side_of_the_persistent_kernel(nt, n):
+    """Integer convolutions at the counts where the form changes: the batch that
+    keeps every CU busy and the one with an item less agree item by item, and
+    with the oracle's integer sums."""
+    N = 1 << n
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = {13: 3, 14: 1025, 15: (4 * cus + 2) // 3, 16: (4 * cus + 2) // 3, 17: (2 * cus + 2) // 3}[n]
+    b = (46 - n) // 2
+    rng = np.random.default_rng(6000 + n)
+    f = rng.integers(0, 1 << b, (rows, N), dtype=np.uint32)
+    g = rng.integers(0, 1 << b, (rows, N), dtype=np.uint32)
+    df, dg = dev(f), dev(g)
+    h = host(nt.conv_crt(df, dg)).reshape(rows, N)
+    less = host(nt.conv_crt(df[:-1].contiguous(), dg[:-1].contiguous())).reshape(rows - 1, N)
+    assert np.array_equal(h[:-1], less)
+    for r in (0, rows - 1):
+        idx = np.unique(np.r_[0, N - 1, rng.integers(0, N, 10)]).astype(np.uint64)
+        assert np.array_equal(h[r][idx.astype(int)], oracle.conv_integer_entries(f[r], g[r], idx))
