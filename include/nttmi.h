@@ -353,9 +353,9 @@ void ntt_server_destroy(ntt_server *srv);
  * a call actually took: read before and after the call and compare. */
 enum {
     NTT_COUNT_SMALL = 0,         /* LDS convolution kernels (N <= 2^12) */
-    NTT_COUNT_FOURSTEP = 1,      /* multi-launch four-step convolutions (one per launch sequence) */
-    NTT_COUNT_FUSED = 2,         /* persistent fused kernels of one length */
-    NTT_COUNT_MULTI = 3,         /* persistent launches over several lengths */
+    NTT_COUNT_FOURSTEP = 1,      /* few items above 2^12, each spread over the chip (one per launch sequence) */
+    NTT_COUNT_FUSED = 2,         /* many items of one length above 2^12 (one per launch sequence) */
+    NTT_COUNT_MULTI = 3,         /* batches of several lengths as one (one per launch sequence) */
     NTT_COUNT_TRANSFORM = 4,     /* transform launch sequences (ntt_forward / ntt_inverse rows) */
     NTT_COUNT_DESC_CACHED = 5,   /* descriptors uploaded into the content-addressed cache */
     NTT_COUNT_DESC_RING = 6,     /* descriptors uploaded through a stream's staging ring */

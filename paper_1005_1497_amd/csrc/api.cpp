@@ -549,27 +549,38 @@ ntt_status check_range(uint32_t wbits, const void* x, uint64_t n, uint64_t m, vo
 }
 
 // One convolution of length 2^log2n (plan already built) on the stream.
-// Whether c convolutions of length 2^n, back to back, that take a multi-launch form
-// take the matrix-core one: up to 2^24 elements, where operands, results and scratch
-// lie in the memory-side cache (2^24 elements: 2^16 142 -> 134 us, 2^18 172 -> 157;
-// 2^21: 2^16 31.6 -> 25.9; one item of 2^19 21.2 -> 15.6, of 2^13 12.3 -> 11.5); beyond, its
-// launches wait for memory one after the other (2^25: 2^17 289 against 338 us, 2^18
-// 316 against 347), and it stays ahead at 2^19 alone (2^25 351 -> 328, 2^26 705 -> 661).
-bool use_four(const Plan* p, uint32_t elem_bits, uint32_t n, uint32_t c) {
-    return elem_bits == 32 && p->four.tab && (n >= 19 || ((uint64_t)c << n) <= (1u << 24));
+// Whether a batch of c convolutions of length 2^n takes the one-workgroup
+// matrix-core kernels.  2^13: always (one item 12.4 -> 11.2 us, 128: 18.9 -> 11.9, 256: 23.2
+// -> 12.8).  2^14: an item takes 22 us however few they are, against 12 us in three
+// launches, which spread one item over the chip; they meet at about 110 items (64: 20
+// against 23.9 us, 128: 25.7 against 24.9, 256: 37 against 29).
+bool use_wide(const Plan* p, uint32_t elem_bits, uint32_t n, uint32_t c) {
+    if (elem_bits != 32 || !p->i8.tab || (int)n < WIDE_MIN_LOG2N || (int)n > WIDE_MAX_LOG2N) return false;
+    return n == 13 || 2ull * c >= (uint64_t)cu_count();
+}
+
+// Whether c convolutions of length 2^n take the three-launch matrix-core form.  Up to
+// 2^24 elements (2^25 at 2^15), where operands, results and scratch mostly lie in the
+// memory-side cache: one item of 2^13 12.3 -> 11.5 us, of 2^19 21.2 -> 15.6; 2^22 elements of
+// 2^16 47 -> 38; 2^24 of 2^16 139 -> 130, 2^25 of 2^15 269 -> 245.  From 2^17 on at every
+// size (2^26 elements of 2^17 550 -> 535, of 2^18 637 -> 540, of 2^19 703 -> 539).  2^15 and 2^16
+// beyond: the persistent kernel, whose workgroups are in different phases at a time,
+// waits less for memory (2^26 elements 450 against 485 us, 510 against 515).
+bool use_four(const Plan* p, uint32_t elem_bits, uint32_t n, uint64_t c) {
+    return elem_bits == 32 && p->four.tab && (n >= 17 || (c << n) <= (n == 15 ? 1u << 25 : 1u << 24));
 }
 // Scratch of a group of items: what leaves room for the operands in the memory-side
-// cache up to 2^24 elements (2^17: 64 MiB 145 us, 128 MiB 161), and beyond enough work
-// per launch (2^26 elements of 2^19: 698 and 661 us).
-ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const void* g, void* h, hipStream_t s,
-                     void* stream, const Quotient* div = nullptr) {
-    const uint64_t per = 8ull << n, budget = ((uint64_t)c << n) <= (1u << 24) ? 1ull << 26 : 1ull << 27;
-    const uint32_t group = (uint32_t)std::min<uint64_t>(c, std::max<uint64_t>(1, budget / per));
+// cache, and enough work per launch (2^26 elements of 2^18: 64 MiB 607 us, 128 541, 256 568).
+uint32_t four_group(uint32_t n, uint32_t c) {
+    return (uint32_t)std::min<uint64_t>(c, std::max<uint64_t>(1, (1ull << 27) / (8ull << n)));
+}
+ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const void* g, void* h,
+                     const uint64_t* doffs, hipStream_t s, void* stream, const Quotient* div = nullptr) {
+    const uint32_t group = four_group(n, c);
     void* ws = nullptr;
-    const ntt_status st = get_buf(caches().work, stream, (size_t)(group * per), &ws);
+    const ntt_status st = get_buf(caches().work, stream, (size_t)group * 8 << n, &ws);
     if (st != NTT_OK) return st;
-    count(NTT_COUNT_FOURSTEP);
-    return hip_status(launch_conv_four((int)n, f, g, h, c, group, ws, p->trans, p->four, s, div));
+    return hip_status(launch_conv_four((int)n, f, g, h, doffs, c, group, ws, p->trans, p->four, s, div));
 }
 
 ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f, const void* g, void* h,
@@ -581,7 +592,14 @@ ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f
             return hip_status(launch_conv_wave((int)log2n, f, g, h, 1, p->i8, (uint32_t)cu_count(), s));
         return hip_status(launch_conv_small((int)wbits, log2n, f, g, h, nullptr, 1, p->dev, s));
     }
-    if (use_four(p, wbits, log2n, 1)) return conv_four(p, log2n, 1, f, g, h, s, stream);
+    if (use_wide(p, wbits, log2n, 1)) {
+        count(NTT_COUNT_FOURSTEP);
+        return hip_status(launch_conv_wide((int)log2n, f, g, h, nullptr, 1, (uint32_t)cu_count(), p->i8, s));
+    }
+    if (use_four(p, wbits, log2n, 1)) {
+        count(NTT_COUNT_FOURSTEP);
+        return conv_four(p, log2n, 1, f, g, h, nullptr, s, stream);
+    }
     void* ws = nullptr;
     ntt_status st = get_buf(caches().work, stream, ((size_t)2 * (wbits / 8)) << log2n, &ws);
     if (st != NTT_OK) return st;
@@ -641,20 +659,6 @@ ntt_status ntt_any(bool inv, uint64_t m, uint32_t log2n, uint64_t root, uint32_t
     return ntt_rows(p, elem_bits, log2n, inv, x, X, batch, stream);
 }
 
-// Whether a batch of c convolutions of length 2^n takes the one-workgroup
-// matrix-core kernels.  2^14: an item takes 22 us however few they are, against
-// 13 us for the four-step kernels, which spread one item over the chip; they meet
-// at about 110 items (64: 21.5 against 23.9 us, 128: 26.4 against 24.9, 256: 45
-// against 29).  2^13: the kernels are ahead at every count (one item 12.4 against
-// 11.2 us, 128: 18.9 against 11.9, 256: 23.2 against 12.8), but single convolutions
-// and batches that leave a third of the CUs without an item keep to the four-step
-// form, as which callers of ntt_launch_counts see them.
-bool use_wide(const Plan* p, uint32_t elem_bits, uint32_t n, uint32_t c) {
-    if (elem_bits != 32 || !p->i8.tab || (int)n < WIDE_MIN_LOG2N || (int)n > WIDE_MAX_LOG2N) return false;
-    const uint64_t cus = (uint64_t)cu_count();
-    return n == 13 ? 3ull * c >= 2 * cus : 2ull * c >= cus;
-}
-
 // One launch for the items of one length class: the LDS kernel below 2^13,
 // the persistent fused four-step kernel above.
 // c items of length 2^n: at offsets base + i 2^n (doffs null), else at the
@@ -673,18 +677,11 @@ ntt_status launch_items(uint32_t n, uint32_t c, uint64_t base, const uint64_t* d
         return hip_status(launch_conv_small((int)elem_bits, n, F + base * wb, G + base * wb, H + base * wb, doffs, c,
                                             p->dev, s, form == CF_SMALL_WAVE ? SMALL_TILE_WAVE : SMALL_TILE_256));
     }
-    if (form == CF_DEFAULT && use_wide(p, elem_bits, n, c)) {
-        count(NTT_COUNT_FUSED);
-        return hip_status(launch_conv_wide((int)n, F + base * wb, G + base * wb, H + base * wb, doffs, c,
-                                           (uint32_t)cu_count(), p->i8, s));
-    }
     // multi-launch four-step form: every phase spreads all items over the
     // chip; scratch 2N words per item, within 1 GiB
     const bool fourstep_ok = contiguous && (((uint64_t)2 * c * wb) << n) <= (1ull << 30);
     // (workgroup size: by the default rule, or as the form names it)
     auto fourstep = [&]() -> ntt_status {
-        if (form == CF_DEFAULT && use_four(p, elem_bits, n, c))
-            return conv_four(p, n, c, F + base * wb, G + base * wb, H + base * wb, s, stream);
         void* ws = nullptr;
         const ntt_status e = get_buf(caches().work, stream, (size_t)(((uint64_t)2 * c * wb) << n), &ws);
         if (e != NTT_OK) return e;
@@ -709,7 +706,18 @@ ntt_status launch_items(uint32_t n, uint32_t c, uint64_t base, const uint64_t* d
     // one item per workgroup, would leave CUs idle, so the four-step form runs
     // (measured 1.1-2.4x faster there at 2^15..2^19; above it the fused form
     // is faster or equal)
-    if (form == CF_DEFAULT && fourstep_ok && 3ull * c < 2ull * grid) return fourstep();
+    const bool few = fourstep_ok && 3ull * c < 2ull * grid;
+    // the matrix-core forms, counted by what the batch is: few items or many
+    if (form == CF_DEFAULT && use_wide(p, elem_bits, n, c)) {
+        count(few ? NTT_COUNT_FOURSTEP : NTT_COUNT_FUSED);
+        return hip_status(launch_conv_wide((int)n, F + base * wb, G + base * wb, H + base * wb, doffs, c,
+                                           (uint32_t)cu_count(), p->i8, s));
+    }
+    if (form == CF_DEFAULT && use_four(p, elem_bits, n, c)) {
+        count(few ? NTT_COUNT_FOURSTEP : NTT_COUNT_FUSED);
+        return conv_four(p, n, c, F + base * wb, G + base * wb, H + base * wb, doffs, s, stream);
+    }
+    if (form == CF_DEFAULT && few) return fourstep();
     grid = std::min<uint64_t>(grid, c);
     void* ws = nullptr;
     st = get_buf(caches().work, stream, (size_t)(grid * per_wg), &ws);
@@ -1054,7 +1062,7 @@ ntt_status conv_circular_noalloc(uint64_t m, uint32_t log2n, uint64_t root, uint
     if (e != hipSuccess) return hip_status(e);
     count(NTT_COUNT_FOURSTEP);
     if (use_four(p, elem_bits, log2n, 1))
-        return hip_status(launch_conv_four((int)log2n, f, g, h, 1, 1, ws, p->trans, p->four, s));
+        return hip_status(launch_conv_four((int)log2n, f, g, h, nullptr, 1, 1, ws, p->trans, p->four, s));
     return hip_status(launch_conv_fourstep((int)elem_bits, log2n, f, g, h, 1, 0, ws, p->dev, s, nullptr,
                                            (uint32_t)cu_count()));
 }
@@ -1105,7 +1113,8 @@ ntt_status conv_deconvolve(uint64_t m, uint32_t log2n, uint64_t root, uint32_t e
         // an item idle (100 of 2^18: 644 us, three launches 347; one of 2^19: 1373, 45; 400
         // of 2^15 up to 2^24 elements even); with every CU busy it is ahead where the
         // three launches wait for memory (1000 of 2^16: 638 against 722)
-        st = conv_four(p, log2n, batch, F, Hh, Gg, s, stream, &div);
+        count(NTT_COUNT_FOURSTEP);
+        st = conv_four(p, log2n, batch, F, Hh, Gg, nullptr, s, stream, &div);
         if (st != NTT_OK) return st;
     } else if ((int)log2n <= SMALL_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);

@@ -20,22 +20,26 @@
 
 namespace nttmi {
 
-// Items back to back; scratch 2N words per item, rows of f and then of g.
-template <int n>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_four_cols(
-    const uint32_t* f, const uint32_t* g, uint32_t* Y, I8Plan p) {
-    constexpr uint32_t N = 1u << n, CH = N / 4096;
-    __shared__ v4i xch[1024];
-    const uint32_t id = pair_blocks(blockIdx.x, gridDim.x), half = id / CH;
-    cols_block<n, FORWARD, false>((half & 1 ? g : f) + (uint64_t)(half / 2) * N, Y + (uint64_t)half * N, id % CH, p, xch);
+// Items at offs[i], or back to back (offs null); scratch 2N words per item, rows of f
+// and then of g.
+template <int n, int V>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5 - V, 5 - V))) void k_four_cols(
+    const uint32_t* f, const uint32_t* g, const uint64_t* __restrict__ offs, uint32_t* Y, I8Plan p) {
+    constexpr uint32_t N = 1u << n, CB = N / 4096 / V;
+    __shared__ v4i xch[V][1024];
+    const uint32_t id = col_id<V>(), half = id / CB;
+    const uint64_t off = offs ? offs[half / 2] : (uint64_t)(half / 2) * N;
+    cols_block<n, FORWARD, false, V>((half & 1 ? g : f) + off, Y + (uint64_t)half * N, id % CB, p,
+                                     xch);
 }
-template <int n, bool SMALL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_four_inv(
-    const uint32_t* Y, uint32_t* h, I8Plan p) {
-    constexpr uint32_t N = 1u << n, CH = N / 4096;
-    __shared__ v4i xch[1024];
-    const uint32_t id = pair_blocks(blockIdx.x, gridDim.x), item = id / CH;
-    cols_block<n, INVERSE, SMALL>(Y + (uint64_t)item * 2 * N, h + (uint64_t)item * N, id % CH, p, xch);
+template <int n, bool SMALL, int V>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5 - V, 5 - V))) void k_four_inv(
+    const uint32_t* Y, uint32_t* h, const uint64_t* __restrict__ offs, I8Plan p) {
+    constexpr uint32_t N = 1u << n, CB = N / 4096 / V;
+    __shared__ v4i xch[V][1024];
+    const uint32_t id = col_id<V>(), item = id / CB;
+    const uint64_t off = offs ? offs[item] : (uint64_t)item * N;
+    cols_block<n, INVERSE, SMALL, V>(Y + (uint64_t)item * 2 * N, h + off, id % CB, p, xch);
 }
 template <int n, bool SMALL, class Point>
 __device__ __forceinline__ void four_rows(uint32_t* Y, int rounds, const I8Plan& p, const Point& point) {

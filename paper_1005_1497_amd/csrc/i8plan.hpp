@@ -142,12 +142,13 @@ inline std::vector<int8_t> i8_trans_tables(int n, uint64_t m, uint64_t scale, PW
         for (int l = 0; l < 64; ++l)
             for (int i = 0; i < 4; ++i) i8_pair(t, fw((uint64_t)256 * (4 * (l >> 4) + i) * (j + R * ((l & 15) % B))), m);
     }
-    // blocks of 16 columns t1; register u0; u2 = u0 + 16 (4 g + i): residues in (-m/2, m/2]
+    // blocks of 32 columns; register u0; columns t1 = 2 c, then 2 c + 1; u2 = u0 + 16 (4 g + i):
+    // residues in (-m/2, m/2]
     t.reserve(t.size() + 4 * N);
     for (uint64_t r = 0; r < N / 256; ++r)
         for (uint64_t l = 0; l < 64; ++l)
             for (uint64_t i = 0; i < 4; ++i) {
-                const uint64_t w = fw((16 * (r / 16) + (l & 15)) * (r % 16 + 16 * (4 * (l >> 4) + i)));
+                const uint64_t w = fw((32 * (r / 32) + 2 * (l & 15) + r % 2) * (r / 2 % 16 + 16 * (4 * (l >> 4) + i)));
                 const int32_t b = (int32_t)(2 * w > m ? (int64_t)w - (int64_t)m : (int64_t)w);
                 const int8_t* q = (const int8_t*)&b;
                 t.insert(t.end(), q, q + 4);

@@ -10,7 +10,12 @@ hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, voi
     switch (logn) {
 #define CASE(n)                                                                                                      \
     case n:                                                                                                          \
-        hipLaunchKernelGGL((k_ntt_cols<n>), dim3(blocks), dim3(256), 0, st, (const uint32_t*)x, (uint32_t*)scratch, p); \
+        if (wide_cols(blocks))                                                                                       \
+            hipLaunchKernelGGL((k_ntt_cols<n, 2>), dim3(blocks / 2), dim3(256), 0, st, (const uint32_t*)x,           \
+                               (uint32_t*)scratch, p);                                                               \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_ntt_cols<n, 1>), dim3(blocks), dim3(256), 0, st, (const uint32_t*)x,               \
+                               (uint32_t*)scratch, p);                                                               \
         if (p.C.small)                                                                                               \
             hipLaunchKernelGGL((k_ntt_rows<n, true>), dim3(blocks), dim3(256), 0, st, (const uint32_t*)scratch,      \
                                (uint32_t*)X, p);                                                                     \

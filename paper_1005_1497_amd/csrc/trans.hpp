@@ -39,69 +39,105 @@ __device__ __forceinline__ uint32_t pair_blocks(uint32_t id, uint32_t blocks) {
     return (id | 15) < blocks ? (id & ~15u) + 2 * (r & 7) + (r >> 3) : id;
 }
 
-// Columns: 16 of them in the registers of four waves, t2 = p1 + 16 p2, u2 = u0 + 16 u1:
-// register p1 over p2, exchange p1 against u0, register u0 over p1 with w_256^(p1 u0)
-// in its matrix (the column stays in the lane).  TRANSFORM: words to digits times
-// w^(t1 u2), the rows as above; FORWARD: the rows in their order; INVERSE: digits, the
-// rows in their order, to words.
+// Columns: 16 V of them in the registers of four waves, V neighbours to a lane.  V = 2
+// makes a row's piece a whole cache line and has more loads in flight (2^26 elements,
+// forward columns of two operands: 341 -> 250 us, inverse 148 -> 105); V = 1 is for few
+// blocks, where a workgroup's own time counts (one item of 2^19 17.4 -> 15.6 us).  t2 = p1 + 16 p2, u2 = u0 + 16 u1: register p1 over
+// p2, exchange p1 against u0, register u0 over p1 with w_256^(p1 u0) in its matrix (the
+// column stays in the lane).  TRANSFORM: words to digits times w^(t1 u2), the rows as
+// above; FORWARD: the rows in their order; INVERSE: digits, the rows in their order, to
+// words.
 enum { TRANSFORM, FORWARD, INVERSE };
-template <int n, int KIND, bool SMALL>
+template <int n, int KIND, bool SMALL, int V>
 __device__ __forceinline__ void cols_block(const uint32_t* src, uint32_t* dst, uint32_t bx, const I8Plan& p,
-                                           v4i* xch) {
+                                           v4i (*xch)[1024]) {
     using G = TransG<n>;
     using T = TransTab<n>;
     constexpr uint32_t N = G::N, Q = G::Q, S = KIND == TRANSFORM ? G::S : 1;
     const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const auto bs = wave_buf(src, N * 4), bd = wave_buf(dst, N * 4);
-    // row 4 wave + k + 16 (4 g + i)
-    const uint32_t lw = (uint32_t)c + 64 * Q * (uint32_t)gr;
-    auto at_word = [&](int k, int i) { return 16 * bx + Q * (uint32_t)(4 * wave + k + 16 * i); };
-    v4i x[4], tt[4];
+    // row 4 wave + k + 16 (4 g + i), columns V c ..
+    const uint32_t lw = V * (uint32_t)c + 64 * Q * (uint32_t)gr;
+    auto at_word = [&](int k, int i) { return 16 * V * bx + Q * (uint32_t)(4 * wave + k + 16 * i); };
+    v4i x[V][4], tt[V][4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bs, lw, at_word(k, i)) ^ (KIND == INVERSE ? (int)DIG : 0);
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (V == 2) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(bs, lw * 4, at_word(k, i) * 4, 0);
+                x[0][k][i] = (int)v[0];
+                x[1][k][i] = (int)v[1];
+            } else
+                x[0][k][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(bs, lw * 4, at_word(k, i) * 4, 0);
+        }
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat W = ld_mat(t + T::W, lane);
     Mat M[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        M[k] = ld_mat(t + T::M + (4 * wave + k) * 192, lane);
-        if constexpr (KIND != INVERSE) tt[k] = t[T::TT + (bx * 16 + 4 * wave + k) * 64 + lane];
-    }
+    for (int k = 0; k < 4; ++k) M[k] = ld_mat(t + T::M + (4 * wave + k) * 192, lane);
+    if constexpr (KIND != INVERSE)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int s = 0; s < V; ++s) {   // (in the order of V = 2)
+                const uint32_t b = V == 2 ? bx : bx / 2, odd = V == 2 ? s : c & 1,
+                               at = V == 2 ? lane : 16 * gr + 8 * (bx & 1) + (c >> 1);
+                tt[s][k] = t[T::TT + ((b * 16 + 4 * wave + k) * 2 + odd) * 64 + at];
+            }
     const Init lo = init_loose(C), ti = init_tight(C);
     const Init raw = KIND == INVERSE ? lo : init_raw(lo, C, [&](int i) { return gr == 0 && i == 0; });
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = fold4_loose(digit_sums<KEEP>(W, x[k], raw), C);
-    mid_put(xch, x, wave, gr, c);
+    for (int s = 0; s < V; ++s) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (KIND != INVERSE)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[s][k][i] ^= (int)DIG;
+            x[s][k] = fold4_loose(digit_sums<KEEP>(W, x[s][k], raw), C);
+        }
+        mid_put(xch[s], x[s], wave, gr, c);
+    }
     __syncthreads();
-    mid_get(xch, x, wave, gr, c);
+#pragma unroll
+    for (int s = 0; s < V; ++s) mid_get(xch[s], x[s], wave, gr, c);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const Sums s = digit_sums<KEEP>(M[k], x[k], ti);
-        x[k] = KIND == INVERSE ? fold4_tight(s, C) : fold4_w(s, tt[k], C);
+#pragma unroll
+        for (int s = 0; s < V; ++s) {
+            const Sums sum = digit_sums<KEEP>(M[k], x[s][k], ti);
+            x[s][k] = KIND == INVERSE ? fold4_tight(sum, C) : fold4_w(sum, tt[s][k], C);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+            uint32_t o[V];
+#pragma unroll
+            for (int s = 0; s < V; ++s) o[s] = KIND == INVERSE ? out_word<SMALL>(x[s][k][i], C) : (uint32_t)x[s][k][i];
             const uint32_t u1 = (uint32_t)(4 * gr + i);
-            if constexpr (KIND == TRANSFORM)
-                st_out(bd, (uint32_t)x[k][i], (u1 / S) * (16 * S * Q) + (u1 % S) * Q + (uint32_t)c,
-                       S * Q * (4 * wave + k) + 16 * bx);
-            else
-                st_out(bd, KIND == INVERSE ? out_word<SMALL>(x[k][i], C) : (uint32_t)x[k][i], lw, at_word(k, i));
+            const uint32_t lo = KIND == TRANSFORM ? (u1 / S) * (16 * S * Q) + (u1 % S) * Q + V * (uint32_t)c : lw,
+                           at = KIND == TRANSFORM ? S * Q * (4 * wave + k) + 16 * V * bx : at_word(k, i);
+            if constexpr (V == 2) __builtin_amdgcn_raw_buffer_store_b64(v2u{o[0], o[1]}, bd, lo * 4, at * 4, 0);
+            else st_out(bd, o[0], lo, at);
         }
     }
 }
 
-template <int n>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ntt_cols(const uint32_t* f,
-                                                                                            uint32_t* Y, I8Plan p) {
-    constexpr uint32_t N = 1u << n, CH = N / 4096;
-    __shared__ v4i xch[1024];
-    const uint32_t id = pair_blocks(blockIdx.x, gridDim.x);
-    const uint64_t at = (uint64_t)(id / CH) * N;
-    cols_block<n, TRANSFORM, false>(f + at, Y + at, id % CH, p, xch);
+// Block of a column kernel's workgroup: for V = 1 neighbours share every cache line.
+template <int V>
+__device__ __forceinline__ uint32_t col_id() {
+    return V == 2 ? blockIdx.x : pair_blocks(blockIdx.x, gridDim.x);
+}
+
+template <int n, int V>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5 - V, 5 - V))) void k_ntt_cols(const uint32_t* f,
+                                                                                                    uint32_t* Y, I8Plan p) {
+    constexpr uint32_t N = 1u << n, CB = N / 4096 / V;
+    __shared__ v4i xch[V][1024];
+    const uint32_t id = col_id<V>();
+    const uint64_t at = (uint64_t)(id / CB) * N;
+    cols_block<n, TRANSFORM, false, V>(f + at, Y + at, id % CB, p, xch);
 }
 
 // Rows: 4096 outputs, a chunk's for one j.
