@@ -764,6 +764,19 @@ ntt_status launch_multi(const std::map<uint32_t, std::vector<uint64_t>>& cls,
     }
     std::vector<uint64_t> blob;
     blob.reserve(nitems + ntask_words + 2 + (nmax + 1) * sizeof(DevPlan) / 8);
+    // Lengths that the three-launch form takes go out in launches of their own before
+    // the persistent one, in which an item keeps one workgroup busy (2^15 66 us, 2^19 1.3
+    // ms) and the longest binds the batch: from 2^17 on, and 2^15 and 2^16 where the
+    // persistent launch would leave CUs idle (us; 50 items of 2^6 .. 2^19 1194 -> 154, 2000
+    // 1440 -> 1271; 100 of 2^8 .. 2^16 123 -> 75; with 2^13 and 2^14 apart too, 300 of 2^8 ..
+    // 2^14 go from 42 to 55).
+    const uint64_t all_tasks = ntask_words / 2;
+    const uint64_t resident = (uint64_t)std::max(1, cu_count()) * std::max(1, multi_blocks_per_cu((int)elem_bits));
+    auto apart = [&](uint32_t n, size_t c) {
+        return n >= 15 && use_four(plans[n], elem_bits, n, c) && (n >= 17 || 3 * all_tasks < 2 * resident);
+    };
+    std::vector<std::pair<uint32_t, size_t>> own;   // length, first of its offsets
+    size_t own_bytes = 0;
     std::vector<uint64_t> tasks;
     tasks.reserve(ntask_words);
     uint32_t nbig = 0;
@@ -772,6 +785,12 @@ ntt_status launch_multi(const std::map<uint32_t, std::vector<uint64_t>>& cls,
         if (n > nmax) continue;
         const std::vector<uint64_t>& off = it->second;
         const uint32_t tile = (int)n <= SMALL_MAX_LOG2N ? (uint32_t)multi_tile((int)n) : 1u;
+        if (apart(n, off.size())) {
+            own.emplace_back(n, blob.size());
+            own_bytes = std::max(own_bytes, (size_t)four_group(n, (uint32_t)off.size()) * 8 << n);
+            blob.insert(blob.end(), off.begin(), off.end());
+            continue;
+        }
         if ((int)n > SMALL_MAX_LOG2N) nbig = std::max(nbig, n);
         const size_t first = blob.size();   // the class's items follow in task order
         for (size_t i = 0; i < off.size(); i += tile) {
@@ -782,7 +801,7 @@ ntt_status launch_multi(const std::map<uint32_t, std::vector<uint64_t>>& cls,
         blob.insert(blob.end(), off.begin(), off.end());
     }
     const uint32_t ntasks = (uint32_t)(tasks.size() / 2);
-    if (ntasks == 0) return NTT_OK;
+    if (ntasks == 0 && own.empty()) return NTT_OK;
     const size_t task_at = blob.size();
     blob.insert(blob.end(), tasks.begin(), tasks.end());
     // per-length plans, indexed by log2n
@@ -809,12 +828,19 @@ ntt_status launch_multi(const std::map<uint32_t, std::vector<uint64_t>>& cls,
     grid = std::min<uint64_t>(grid, std::max<uint64_t>(1, (1ull << 30) / (scratch_words * wb)));
     grid = std::min<uint64_t>(grid, ntasks);
     void* ws = nullptr;
-    st = get_buf(caches().work, stream, (size_t)(grid * scratch_words * wb), &ws);
+    st = get_buf(caches().work, stream, std::max(own_bytes, (size_t)(grid * scratch_words * wb)), &ws);
     if (st != NTT_OK) return st;
     uint32_t* q = nullptr;
     st = get_queue(stream, &q);
     if (st != NTT_OK) return st;
     count(NTT_COUNT_MULTI);
+    for (const auto& o : own) {
+        const uint32_t c = (uint32_t)cls.at(o.first).size();
+        const Plan* p = plans[o.first];
+        st = hip_status(launch_conv_four((int)o.first, F, G, H, dblob + o.second, c, four_group(o.first, c), ws, p->trans,
+                                         p->four, s));
+        if (st != NTT_OK) return st;
+    }
     return hip_status(launch_conv_multi((int)elem_bits, F, G, H, dblob + task_at, ntasks, dblob, ws, scratch_words, q,
                                         (uint32_t)grid, (const DevPlan*)(const void*)dplans, s));
 }

@@ -285,3 +285,41 @@ def test_crt_either_side_of_the_persistent_kernel(nt, n):
     for r in (0, rows - 1):
         idx = np.unique(np.r_[0, N - 1, rng.integers(0, N, 10)]).astype(np.uint64)
         assert np.array_equal(h[r][idx.astype(int)], oracle.conv_integer_entries(f[r], g[r], idx))
+
+
+@pytest.mark.parametrize("m", [13631489, 2277377, 14499841])
+@pytest.mark.parametrize("lo,hi,count", [(6, 19, 40), (13, 17, 24), (8, 16, 700)])
+def test_uneven_lengths_apart(nt, m, lo, hi, count):
+    """Batches of several lengths, scattered, whose long ones leave the single persistent
+    launch (all from 2^15 on with few items, from 2^17 on with many), against the
+    convolutions one by one, bit for bit, and untouched words between the items."""
+    hi = min(hi, nt.max_log2n(m))
+    rng = np.random.default_rng(7000 + hi + count)
+    logs = rng.integers(lo, hi + 1, size=count)
+    logs[:2] = hi
+    rng.shuffle(logs)
+    sizes = (1 << logs) + 64                                  # a gap after each item
+    offs = np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)
+    total = int(sizes.sum())
+    f = rng.integers(0, 1 << 32, size=total, dtype=np.uint64).astype(np.uint32)
+    g = rng.integers(0, 1 << 32, size=total, dtype=np.uint64).astype(np.uint32)
+    order = nt.max_log2n(m)
+    kw = dict(root=nt.euler_root(m, order), root_log2order=order)
+    desc = nt.BatchDesc(logs, offs)
+    df, dg = dev(f), dev(g)
+    outs = []
+    for flags in (nt.FLAG_EULER, nt.FLAG_EULER | nt.FLAG_PER_ITEM):
+        before = nt.launch_counts()["multi"]
+        out = dev(np.full(total, 0xABCDEF01, np.uint32))
+        nt.conv_batched(df, dg, desc, m, out=out, flags=flags, **kw)
+        outs.append(host(out))
+        assert nt.launch_counts()["multi"] == before + (flags == nt.FLAG_EULER)
+    assert np.array_equal(*outs)
+    for n, o in zip(logs, offs):
+        N, o = 1 << int(n), int(o)
+        assert np.all(outs[0][o + N:o + N + 64] == 0xABCDEF01)
+    for i in rng.integers(0, count, 6):
+        N, o = 1 << int(logs[i]), int(offs[i])
+        idx = np.unique(np.r_[0, N - 1, rng.integers(0, N, 10)]).astype(np.uint64)
+        ref = oracle.conv_entries(f[o:o + N] % m, g[o:o + N] % m, m, idx)
+        assert np.array_equal(outs[0][o:o + N][idx.astype(int)], ref.astype(np.uint32))
