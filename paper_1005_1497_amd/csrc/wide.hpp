@@ -159,7 +159,7 @@ __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g,
 #pragma unroll
         for (int q = 0; q < PW; ++q) out[q] = fold4_loose(sums(A, v[q], in), C);
     };
-    auto mats = [&](Mat (&A)[R], int at, int step) {   // (j = 0, k = 0: no factors w_R^(j k))
+    auto mats = [&](Mat (&A)[R], int at, int step) {
 #pragma unroll
         for (int k = 0; k < R; ++k) A[k] = ld_mat(ts + T::J + at + k * step, lane);
     };
@@ -170,7 +170,11 @@ __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g,
 #pragma unroll
         for (int k = 0; k < R; ++k) {
             Mat B[R];
-            if (k + 1 < R) mats(B, T::L(R) + (k + 1) * 192, T::size(R));
+            if (k + 1 < R) {
+                B[0] = A[0];   // (j = 0: no factors w_R^(j k))
+#pragma unroll
+                for (int j = 1; j < R; ++j) B[j] = ld_mat(tab(j) + T::L(R) + (k + 1) * 192, lane);
+            }
 #pragma unroll
             for (int q = 0; q < PW; ++q) {
                 const v4i r = fold4_tight(sums(A, a[q], ti), C);
@@ -238,8 +242,11 @@ __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g,
             digits(gw);
 #pragma unroll
             for (int j = 0; j < R; ++j) {
+                // (w_R^(j k) repeats with k: R / gcd(j, R) matrices)
                 Mat A[R];
-                mats(A, j * T::size(R) + T::F, 192);
+                const int per = j == 0 ? 1 : j == 2 ? 2 : 4;
+#pragma unroll
+                for (int k = 0; k < R; ++k) A[k] = k < per ? ld_mat(tab(j) + T::F + k * 192, lane) : A[k % per];
                 v4i x[PW];
                 first(j, A, fr, x);
                 wide_put<PW>(xch[j], x, wave, gr, c);
