@@ -575,12 +575,13 @@ uint32_t four_group(uint32_t n, uint32_t c) {
     return (uint32_t)std::min<uint64_t>(c, std::max<uint64_t>(1, (1ull << 27) / (8ull << n)));
 }
 ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const void* g, void* h,
-                     const uint64_t* doffs, hipStream_t s, void* stream, const Quotient* div = nullptr) {
+                     const uint64_t* doffs, hipStream_t s, void* stream, const Quotient* div = nullptr,
+                     const Combine* crt = nullptr) {
     const uint32_t group = four_group(n, c);
     void* ws = nullptr;
     const ntt_status st = get_buf(caches().work, stream, (size_t)group * 8 << n, &ws);
     if (st != NTT_OK) return st;
-    return hip_status(launch_conv_four((int)n, f, g, h, doffs, c, group, ws, p->trans, p->four, s, div));
+    return hip_status(launch_conv_four((int)n, f, g, h, doffs, c, group, ws, p->trans, p->four, s, div, crt));
 }
 
 ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f, const void* g, void* h,
@@ -1200,8 +1201,7 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     st = get_plan(m1, log2n, r1, l1, &p1);
     if (st == NTT_OK) st = get_plan(m2, log2n, r2, l2, &p2);
     if (st != NTT_OK) return st;
-    // residues mod m1, then the convolution mod m2; a pass that combines both, or
-    // the persistent kernel's store that does
+    // residues mod m1, then the convolution mod m2 and the combination of both
     void* tmp = nullptr;
     st = get_buf(caches().tune, stream, 2 * in_bytes, &tmp);
     if (st != NTT_OK) return st;
@@ -1211,13 +1211,20 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     const uint32_t c = (uint32_t)powmod64(m1 % m2, m2 - 2, m2);   // m1^-1 mod m2
     st = launch_items(log2n, batch, 0, nullptr, p1, 32, (const char*)f, (const char*)g, (char*)a1, s, stream, CF_DEFAULT);
     if (st != NTT_OK) return st;
-    // The persistent kernel's combining store saves a pass over both residues, but
-    // leaves an item to one workgroup: it is for lengths from 2^14 on with every CU busy
-    // (us, two convolutions and a combining pass / persistent: 1000 of 2^13 90 / 130,
-    // 8192 717 / 791; 800 of 2^14 221 / 236, 4096 945 / 914; 200 of 2^15 130 / 149, 400
-    // 282 / 268; 128 of 2^17 377 / 470, 256 663 / 634; one of 2^19 34 / 1297)
+    // From 2^14 on the second convolution's store combines both residues: that of the
+    // three-launch form, or with every CU busy, where that form waits for memory, that of
+    // the persistent kernel (us, three launches / persistent: 800 of 2^14 203 / 287, 4096 944 /
+    // 914; 600 of 2^15 347 / 382, 2048 1042 / 990; 300 of 2^16 367 / 415, 512 574 / 560; 512 of
+    // 2^17 1182 / 1230; one of 2^19 34 / 1303).  Below, two convolutions and a combining
+    // pass (1000 of 2^13 90 us, against 191 with the persistent kernel).
     uint64_t grid = log2n < 14 ? 0 : (uint64_t)std::max(1, cu_count()) * std::max(1, fused_blocks_per_cu(32, (int)log2n));
-    if (log2n == 14 ? batch > 1024 : log2n > 14 && 3ull * batch >= 2 * grid) {
+    if (log2n >= 14 && (use_four(p2, 32, log2n, batch) || 3ull * batch < 2 * grid)) {
+        const int32_t cb = 2 * (uint64_t)c > m2 ? (int32_t)c - (int32_t)m2 : (int32_t)c;
+        const Combine crt{a1, (uint64_t*)h, (uint32_t)m1, cb, (float)(-(double)cb / (double)m2)};
+        count(NTT_COUNT_FOURSTEP);
+        return conv_four(p2, log2n, batch, f, g, nullptr, nullptr, s, stream, nullptr, &crt);
+    }
+    if (log2n >= 14) {
         const uint64_t per_wg = (uint64_t)2 * 4 << log2n;
         grid = std::min<uint64_t>(grid, std::max<uint64_t>(1, (1ull << 30) / per_wg));
         grid = std::min<uint64_t>(grid, batch);

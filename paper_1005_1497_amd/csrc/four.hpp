@@ -41,6 +41,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5 - V, 5 - 
     const uint64_t off = offs ? offs[item] : (uint64_t)item * N;
     cols_block<n, INVERSE, SMALL, V>(Y + (uint64_t)item * 2 * N, h + off, id % CB, p, xch);
 }
+template <int n, int V>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5 - V, 5 - V))) void k_four_crt(const uint32_t* Y,
+                                                                                                    Combine crt, I8Plan p) {
+    constexpr uint32_t N = 1u << n, CB = N / 4096 / V;
+    __shared__ v4i xch[V][1024];
+    const uint32_t id = col_id<V>(), item = id / CB;
+    crt.h += (uint64_t)item * N;
+    cols_block<n, INVERSE, false, V, true>(Y + (uint64_t)item * 2 * N, (uint32_t*)crt.a1 + (uint64_t)item * N, id % CB, p,
+                                           xch, crt);
+}
 template <int n, bool SMALL, class Point>
 __device__ __forceinline__ void four_rows(uint32_t* Y, int rounds, const I8Plan& p, const Point& point) {
     constexpr int la = n - 8;

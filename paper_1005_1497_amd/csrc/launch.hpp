@@ -18,6 +18,16 @@ struct DevPlan {
     int logn, nmask;
 };
 
+// The combining store of integer convolutions: h = a1 + m1 ((a2 - a1) c mod m2) for the
+// residues a1 modulo m1 in memory and a2 modulo m2, the launch's own modulus.
+struct Combine {
+    const uint32_t* a1;
+    uint64_t* h;
+    uint32_t m1;
+    int32_t c;   // m1^-1 mod m2, in (-m2/2, m2/2], and -c / m2
+    float cq;
+};
+
 // Constants of the matrix-core transforms of 32-bit words (i8dft.hpp) modulo m.
 struct I8C {
     uint32_t m;
@@ -104,10 +114,11 @@ hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, voi
 // Convolutions of lengths TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N of 32-bit words in three
 // launches per `group` items, at offs[i] or back to back (offs null).  trans: the transforms' plans of the length,
 // forward and inverse; rows: tables of the rows (tab) and twiddles (tti); scratch:
-// min(group, count) * 2N words.
+// min(group, count) * 2N words.  crt: the combining store (h unused; items back to back;
+// moduli from 2^21 on).
 hipError_t launch_conv_four(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count, uint32_t group,
                             void* scratch, const I8Plan* trans, const I8Plan& rows, hipStream_t st,
-                            const Quotient* div = nullptr);
+                            const Quotient* div = nullptr, const Combine* crt = nullptr);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
                             hipStream_t st);
 // scratch: items * 2N scratch words (conv), batch * N (ntt); scratch words are

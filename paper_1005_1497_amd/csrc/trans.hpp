@@ -48,9 +48,11 @@ __device__ __forceinline__ uint32_t pair_blocks(uint32_t id, uint32_t blocks) {
 // above; FORWARD: the rows in their order; INVERSE: digits, the rows in their order, to
 // words.
 enum { TRANSFORM, FORWARD, INVERSE };
-template <int n, int KIND, bool SMALL, int V>
+// CRT: INVERSE with the combining store instead (dst: this item's residues of the other
+// modulus, read only; crt.h: its results).
+template <int n, int KIND, bool SMALL, int V, bool CRT = false>
 __device__ __forceinline__ void cols_block(const uint32_t* src, uint32_t* dst, uint32_t bx, const I8Plan& p,
-                                           v4i (*xch)[1024]) {
+                                           v4i (*xch)[1024], const Combine& crt = Combine{}) {
     using G = TransG<n>;
     using T = TransTab<n>;
     constexpr uint32_t N = G::N, Q = G::Q, S = KIND == TRANSFORM ? G::S : 1;
@@ -72,6 +74,18 @@ __device__ __forceinline__ void cols_block(const uint32_t* src, uint32_t* dst, u
             } else
                 x[0][k][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(bs, lw * 4, at_word(k, i) * 4, 0);
         }
+    uint32_t a1[CRT ? 4 : 1][4][V];
+    if constexpr (CRT)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (V == 2) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(bd, lw * 4, at_word(k, i) * 4, 0);
+                    a1[k][i][0] = v[0], a1[k][i][1] = v[1];
+                } else
+                    a1[k][i][0] = __builtin_amdgcn_raw_buffer_load_b32(bd, lw * 4, at_word(k, i) * 4, 0);
+            }
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat W = ld_mat(t + T::W, lane);
@@ -118,7 +132,23 @@ __device__ __forceinline__ void cols_block(const uint32_t* src, uint32_t* dst, u
             const uint32_t u1 = (uint32_t)(4 * gr + i);
             const uint32_t lo = KIND == TRANSFORM ? (u1 / S) * (16 * S * Q) + (u1 % S) * Q + V * (uint32_t)c : lw,
                            at = KIND == TRANSFORM ? S * Q * (4 * wave + k) + 16 * V * bx : at_word(k, i);
-            if constexpr (V == 2) __builtin_amdgcn_raw_buffer_store_b64(v2u{o[0], o[1]}, bd, lo * 4, at * 4, 0);
+            if constexpr (CRT) {
+                const auto bh = wave_buf(crt.h, N * 8);
+                uint64_t r[V];
+#pragma unroll
+                for (int s = 0; s < V; ++s) {
+                    const int b = reduce_i((int)o[s] - (int)a1[k][i][s], C);   // (both below 2^24)
+                    const float q = __builtin_fmaf((float)b, crt.cq, MAGIC);
+                    const uint32_t t = canon_i((int32_t)mad24u(fbits(q), C.m, mad24s(b, crt.c, (uint32_t)C.it)), C);
+                    r[s] = a1[k][i][s] + (uint64_t)crt.m1 * t;
+                }
+                const v2u r0{(uint32_t)r[0], (uint32_t)(r[0] >> 32)};
+                if constexpr (V == 2)
+                    st_out4(bh, v4u{r0[0], r0[1], (uint32_t)r[1], (uint32_t)(r[1] >> 32)}, (lo + at) * 2);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b64(r0, bh, lo * 8, at * 8, 0);
+            } else if constexpr (V == 2)
+                __builtin_amdgcn_raw_buffer_store_b64(v2u{o[0], o[1]}, bd, lo * 4, at * 4, 0);
             else st_out(bd, o[0], lo, at);
         }
     }
@@ -195,13 +225,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     mid_put(xch, o, wave, gr, c);
     __syncthreads();
     mid_get(xch, o, wave, gr, c);
-    typedef unsigned v4u __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const uint32_t u1 = j + R * ((uint32_t)c % B + B * (uint32_t)(4 * wave + k));
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o[k]), bh,
-                                               (4 * (uint32_t)gr + 16 * ((uint32_t)c / B) + 256 * u1) * 4,
-                                               16 * S * q * 4, 0);
+        st_out4(bh, __builtin_bit_cast(v4u, o[k]), 4 * (uint32_t)gr + 16 * ((uint32_t)c / B) + 256 * u1 + 16 * S * q);
     }
 }
 

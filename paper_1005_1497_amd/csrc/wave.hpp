@@ -27,6 +27,13 @@ __device__ __forceinline__ int ld_raw(__amdgpu_buffer_rsrc_t b, uint32_t lane_wo
 __device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uint32_t lane_word, uint32_t word) {
     __builtin_amdgcn_raw_buffer_store_b32(x, b, lane_word * 4, word * 4, 0);
 }
+// Sixteen bytes at once.  With a scalar register as offset the compiler would leave no
+// wait before the next write to the stored registers, and the last lanes of the store
+// read what that write put there; all of the offset is in the lanes.
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void st_out4(__amdgpu_buffer_rsrc_t b, v4u x, uint32_t word) {
+    __builtin_amdgcn_raw_buffer_store_b128(x, b, word * 4, 0, 0);
+}
 
 // The pointwise steps over four registers of spectra (tight residues).
 // x <- x y, as digits:

@@ -268,12 +268,12 @@ def test_quotients(nt, n, m):
 
 @pytest.mark.parametrize("n", [13, 14, 15, 16, 17])
 def test_crt_either_side_of_the_persistent_kernel(nt, n):
-    """Integer convolutions at the counts where the form changes: the batch that
-    keeps every CU busy and the one with an item less agree item by item, and
-    with the oracle's integer sums."""
+    """Integer convolutions at the counts where the form changes: the batch that the
+    persistent kernel takes and the one with an item less agree item by item, and
+    with the oracle's integer sums (2^13 and 2^17: one form at every count)."""
     N = 1 << n
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    rows = {13: 3, 14: 1025, 15: (4 * cus + 2) // 3, 16: (4 * cus + 2) // 3, 17: (2 * cus + 2) // 3}[n]
+    rows = {13: 3, 14: 1025, 15: 1025, 16: (4 * cus + 2) // 3, 17: 3}[n]
     b = (46 - n) // 2
     rng = np.random.default_rng(6000 + n)
     f = rng.integers(0, 1 << b, (rows, N), dtype=np.uint32)
