@@ -7,14 +7,13 @@
 //   inverse columns: length-256 inverse transforms over u2, canonical store.
 // The frequency order stays inside, so nothing is transposed in memory.  Memory moves
 // 16, 12 and 8 bytes per element; the columns and the inverse columns are bound by
-// that (49 and 25 us per 2^24 elements), the rows by vector issue (47 us, 57 above 2^16).
-// m = 13631489, against the fp64 four-step kernels: one item of 2^13 12.3 -> 11.5 us, of
-// 2^16 13.1 -> 11.8, of 2^19 21.2 -> 15.6; 2^22 elements of 2^16 48 -> 38, of 2^19 61 -> 42;
-// 2^24 elements of 2^18 172 -> 151.  Slower: the phases of successive groups side by
-// side in one launch (2^24 elements of 2^16 162 us against 134; its columns then have
-// three waves per SIMD, not four), and workgroups of one die that keep an item's
-// scratch in its L2 and wait for each other between the phases (2^26 elements 660
-// against 610).
+// that (62 and 24 us per 2^24 elements, 4.3 and 5.6 TB/s), the rows by vector issue (46
+// us, 60 above 2^16).  m = 13631489, against the fp64 four-step kernels: one item of 2^16
+// 13.2 -> 12.0 us, of 2^19 21.2 -> 15.6; 2^22 elements of 2^16 48 -> 38, of 2^19 61 -> 41; 2^24
+// of 2^18 172 -> 138; 2^26 of 2^18 637 -> 540, of 2^19 703 -> 539.  Slower: the phases of
+// successive groups side by side in one launch (2^24 elements of 2^16 162 us against 130),
+// and workgroups of one die that keep an item's scratch in its L2 and wait for each
+// other between the phases (2^26 elements of 2^16 660 against 513).
 #pragma once
 #include "trans.hpp"
 

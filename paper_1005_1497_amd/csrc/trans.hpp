@@ -12,8 +12,8 @@
 // Both launches move 8 bytes per element (the scratch in the memory-side cache) and
 // are bound by that up to R = 4; at R = 8 by the first step's matrix instructions.
 // Forward / inverse, m = 13631489, 2^24 elements, against the fp64 four-step
-// kernels: 2^13 74 / 127 -> 49 / 49 us, 2^16 78 / 100 -> 51 / 50, 2^18 81 / 93 -> 60 / 59,
-// 2^19 107 / 139 -> 81 / 78; one row of 2^16 9.2 / 9.8 -> 6.8 / 6.9.
+// kernels: 2^13 74 / 127 -> 47 / 47 us, 2^16 79 / 100 -> 48 / 48, 2^19 107 / 140 -> 77 / 75; 2^26
+// of 2^16 304 / 400 -> 209 / 208; one row of 2^16 9.2 / 9.8 -> 6.9 / 6.9.
 #pragma once
 #include "wave.hpp"
 

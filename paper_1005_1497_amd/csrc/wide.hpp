@@ -16,11 +16,11 @@
 // buffer and 16 registers.  Bound by vector issue, as k_conv_mid (81 vector and 9
 // matrix instructions per element, three waves per SIMD).  2^26 elements,
 // m = 13631489, against the fp64 kernels with a scratch in memory (36 bytes per
-// element): 447 -> 270 us; 2^24: 137 -> 66.
+// element): 447 -> 267 us; 2^24: 137 -> 64.
 // 2^14: eight waves of 240 registers and all 160 KB of a CU's LDS, two groups of
 // waves with two transforms each; the next item's words are loaded during the last
 // step.  Bound by its two waves per SIMD going through the matrix-heavy first and
-// last steps together.  2^26 elements 463 -> 370 us, 2^24: 152 -> 93.
+// last steps together.  2^26 elements 463 -> 359 us, 2^24: 152 -> 90.
 // A step of its own over k, exchanged through LDS, took 102 vector instructions per
 // element and 370 us at 2^13, 385 at 2^14; with 128 registers (16 waves per CU) it
 // spilled and took 532 and 641.  2^15 and 2^16 that way: 488 and 990 us, no gain over
