@@ -33,7 +33,7 @@ inline void i8_matrix(std::vector<int8_t>& out, uint64_t m, F entry) {
                 int8_t d[3];
                 i8_digits(x, m, d);
                 for (int c = 0; c < 3; ++c) out[at + (size_t)(c * 64 + l) * 16 + 4 * i + a] = d[c];
-                x = mulmod64(x, 256, m);
+                x = x * 256 % m;
             }
         }
 }
@@ -68,6 +68,21 @@ inline I8C make_i8c(uint64_t m, int radix) {
     C.c1 = d[1];
     C.c2 = d[2];
     return C;
+}
+
+// Appends N residues w(r, l, i) (r < N / 256, lane l, i < 4) as words in (-m/2, m/2].
+template <class F>
+inline void i8_words(std::vector<int8_t>& out, uint64_t N, uint64_t m, F w) {
+    const size_t at = out.size();
+    out.resize(at + 4 * N);
+    int8_t* p = &out[at];
+    for (uint64_t r = 0; r < N / 256; ++r)
+        for (uint64_t l = 0; l < 64; ++l)
+            for (uint64_t i = 0; i < 4; ++i, p += 4) {
+                const uint64_t x = w(r, l, i);
+                const int32_t b = (int32_t)(2 * x > m ? (int64_t)x - (int64_t)m : (int64_t)x);
+                std::memcpy(p, &b, 4);
+            }
 }
 
 // Tables of the kernels in wave.hpp; w^e = P(e) for e < N.
@@ -144,15 +159,9 @@ inline std::vector<int8_t> i8_trans_tables(int n, uint64_t m, uint64_t scale, PW
     }
     // blocks of 32 columns; register u0; columns t1 = 2 c, then 2 c + 1; u2 = u0 + 16 (4 g + i):
     // residues in (-m/2, m/2]
-    t.reserve(t.size() + 4 * N);
-    for (uint64_t r = 0; r < N / 256; ++r)
-        for (uint64_t l = 0; l < 64; ++l)
-            for (uint64_t i = 0; i < 4; ++i) {
-                const uint64_t w = fw((32 * (r / 32) + 2 * (l & 15) + r % 2) * (r / 2 % 16 + 16 * (4 * (l >> 4) + i)));
-                const int32_t b = (int32_t)(2 * w > m ? (int64_t)w - (int64_t)m : (int64_t)w);
-                const int8_t* q = (const int8_t*)&b;
-                t.insert(t.end(), q, q + 4);
-            }
+    i8_words(t, N, m, [&](uint64_t r, uint64_t l, uint64_t i) {
+        return fw((32 * (r / 32) + 2 * (l & 15) + r % 2) * (r / 2 % 16 + 16 * (4 * (l >> 4) + i)));
+    });
     *C = make_i8c(m, 16);
     return t;
 }
@@ -166,24 +175,17 @@ inline std::vector<int8_t> i8_four_tables(int n, uint64_t m, uint64_t ninv, PW P
     const uint64_t N = 1ull << n, A = 1ull << la;
     std::vector<int8_t> t = i8_wave_tables(la, m, ninv, [&](uint64_t e) { return P(256 * e); }, C);
     *tti = t.size();
-    t.reserve(t.size() + 4 * N);
-    for (uint64_t r = 0; r < N / 256; ++r)
-        for (uint64_t l = 0; l < 64; ++l)
-            for (uint64_t i = 0; i < 4; ++i) {
-                const uint64_t k = 4 * (l >> 4) + i, c = l & 15;
-                // the element's place in the scratch: blocks of 256 in order, or
-                // chunks of 4096 whose registers are (row, v1)
-                uint64_t e;
-                if (la <= 8) e = 256 * r + 16 * k + c;
-                else {
-                    const uint64_t R1 = A / 256, q = r % 16;
-                    e = 4096 * (r / 16) + (q / R1) * A + c + 16 * (q % R1) + 16 * R1 * k;
-                }
-                const uint64_t w = P((0 - (e & (A - 1)) * (e >> la)) & (N - 1));
-                const int32_t b = (int32_t)(2 * w > m ? (int64_t)w - (int64_t)m : (int64_t)w);
-                const int8_t* q = (const int8_t*)&b;
-                t.insert(t.end(), q, q + 4);
-            }
+    i8_words(t, N, m, [&](uint64_t r, uint64_t l, uint64_t i) {
+        const uint64_t k = 4 * (l >> 4) + i, c = l & 15;
+        // the element's place in the scratch: blocks of 256 in order, or chunks of
+        // 4096 whose registers are (row, v1)
+        uint64_t e = 256 * r + 16 * k + c;
+        if (la > 8) {
+            const uint64_t R1 = A / 256, q = r % 16;
+            e = 4096 * (r / 16) + (q / R1) * A + c + 16 * (q % R1) + 16 * R1 * k;
+        }
+        return P((0 - (e & (A - 1)) * (e >> la)) & (N - 1));
+    });
     return t;
 }
 
