@@ -1203,7 +1203,7 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     if (st != NTT_OK) return st;
     // residues mod m1, then the convolution mod m2 and the combination of both
     void* tmp = nullptr;
-    st = get_buf(caches().tune, stream, 2 * in_bytes, &tmp);
+    st = get_buf(caches().tune, stream, ((int)log2n < WAVE_MIN_LOG2N ? 2 : 1) * in_bytes, &tmp);
     if (st != NTT_OK) return st;
     uint32_t* a1 = (uint32_t*)tmp;
     uint32_t* a2 = a1 + (size_t)batch * N;
@@ -1211,16 +1211,24 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     const uint32_t c = (uint32_t)powmod64(m1 % m2, m2 - 2, m2);   // m1^-1 mod m2
     st = launch_items(log2n, batch, 0, nullptr, p1, 32, (const char*)f, (const char*)g, (char*)a1, s, stream, CF_DEFAULT);
     if (st != NTT_OK) return st;
-    // From 2^14 on the second convolution's store combines both residues: that of the
-    // three-launch form, or with every CU busy, where that form waits for memory, that of
+    // The second convolution's store combines both residues (us, against a pass of its
+    // own: 65536 of 2^8 135 -> 121, 4096 of 2^12 158 -> 129, 1000 of 2^13 90 -> 78).  From 2^14 on it
+    // is that of the three-launch form, or with every CU busy, where that form waits for memory, that of
     // the persistent kernel (us, three launches / persistent: 800 of 2^14 203 / 287, 4096 944 /
     // 914; 600 of 2^15 347 / 382, 2048 1042 / 990; 300 of 2^16 367 / 415, 512 574 / 560; 512 of
-    // 2^17 1182 / 1230; one of 2^19 34 / 1303).  Below, two convolutions and a combining
-    // pass (1000 of 2^13 90 us, against 191 with the persistent kernel).
+    // 2^17 1182 / 1230; one of 2^19 34 / 1303).
     uint64_t grid = log2n < 14 ? 0 : (uint64_t)std::max(1, cu_count()) * std::max(1, fused_blocks_per_cu(32, (int)log2n));
+    const int32_t cb = 2 * (uint64_t)c > m2 ? (int32_t)c - (int32_t)m2 : (int32_t)c;
+    const Combine crt{a1, (uint64_t*)h, (uint32_t)m1, cb, (float)(-(double)cb / (double)m2)};
+    if ((int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WAVE_MAX_LOG2N) {
+        count(NTT_COUNT_SMALL);
+        return hip_status(launch_conv_wave((int)log2n, f, g, nullptr, batch, p2->i8, (uint32_t)cu_count(), s, nullptr, &crt));
+    }
+    if (log2n == 13) {
+        count(NTT_COUNT_FUSED);
+        return hip_status(launch_conv_wide(13, f, g, nullptr, nullptr, batch, (uint32_t)cu_count(), p2->i8, s, nullptr, &crt));
+    }
     if (log2n >= 14 && (use_four(p2, 32, log2n, batch) || 3ull * batch < 2 * grid)) {
-        const int32_t cb = 2 * (uint64_t)c > m2 ? (int32_t)c - (int32_t)m2 : (int32_t)c;
-        const Combine crt{a1, (uint64_t*)h, (uint32_t)m1, cb, (float)(-(double)cb / (double)m2)};
         count(NTT_COUNT_FOURSTEP);
         return conv_four(p2, log2n, batch, f, g, nullptr, nullptr, s, stream, nullptr, &crt);
     }

@@ -89,9 +89,10 @@ hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, 
                              uint32_t* singular = nullptr);
 // The wave kernels (matrix cores): `count` convolutions of length 2^logn
 // (WAVE_MIN_LOG2N .. WAVE_MAX_LOG2N) of 32-bit words back to back.
-// div: the quotients g / f instead (exact deconvolutions).
+// div: the quotients g / f instead (exact deconvolutions); crt: the combining store (h
+// unused; moduli from 2^21 on; of the next launcher 2^13 alone).
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
-                            uint32_t cus, hipStream_t st, const Quotient* div = nullptr);
+                            uint32_t cus, hipStream_t st, const Quotient* div = nullptr, const Combine* crt = nullptr);
 // Forward or inverse transforms of `batch` rows of length 2^logn (WAVE_MIN_LOG2N
 // .. WAVE_MAX_LOG2N) of 32-bit words back to back, natural order.
 hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& p, uint32_t cus,
@@ -101,7 +102,8 @@ hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t 
 // 2^14 at a time.
 constexpr int WIDE_MIN_LOG2N = 13, WIDE_MAX_LOG2N = 14;
 hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count,
-                            uint32_t cus, const I8Plan& p, hipStream_t st, const Quotient* div = nullptr);
+                            uint32_t cus, const I8Plan& p, hipStream_t st, const Quotient* div = nullptr,
+                            const Combine* crt = nullptr);
 // Transforms of `rows` rows of length 2^logn (TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N)
 // of 32-bit words back to back, the direction that of p's tables; scratch: rows * N
 // words.  x and X may be the same.

@@ -16,7 +16,7 @@ static int tiny_rounds(uint64_t words, uint32_t cus) {
 }
 
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
-                            uint32_t cus, hipStream_t st, const Quotient* div) {
+                            uint32_t cus, hipStream_t st, const Quotient* div, const Combine* crt) {
     if (count == 0) return hipSuccess;
     const uint64_t words = (uint64_t)count << logn;
     const uint32_t *ff = (const uint32_t*)f, *gg = (const uint32_t*)g;
@@ -24,6 +24,25 @@ hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uin
     const int rounds = tiny_rounds(words, cus);   // above 2^8: a workgroup per chunk
     const uint64_t share = 4ull * rounds * 256 * TINY_BLOCKS;
     const dim3 tiny((uint32_t)((words + share - 1) / share)), mid((uint32_t)((words + 4095) / 4096)), wg(256);
+    if (crt) {
+        if (p.C.small || div) return hipErrorInvalidValue;
+        switch (logn) {
+#define TINY(n)                                                                                             \
+    case n:                                                                                                 \
+        hipLaunchKernelGGL((k_crt_tiny<n>), tiny, wg, 0, st, ff, gg, words, rounds, p, *crt);               \
+        break;
+#define MID(n)                                                                                              \
+    case n:                                                                                                 \
+        hipLaunchKernelGGL((k_crt_mid<n>), mid, wg, 0, st, ff, gg, words, p, *crt);                         \
+        break;
+            TINY(5) TINY(6) TINY(7) TINY(8) MID(9) MID(10) MID(11) MID(12)
+#undef TINY
+#undef MID
+            default:
+                return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (logn * 4 + (div ? 2 : 0) + (p.C.small ? 1 : 0)) {
 #define TINY(n, s)                                                                                          \
     case n * 4 + s:                                                                                         \

@@ -4,7 +4,8 @@
 namespace nttmi {
 
 hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count,
-                            uint32_t cus, const I8Plan& p, hipStream_t st, const Quotient* div) {
+                            uint32_t cus, const I8Plan& p, hipStream_t st, const Quotient* div,
+                            const Combine* crt) {
     if (count == 0) return hipSuccess;
     // 2^14: one workgroup takes a CU (160 KB of LDS) and loads ahead of its next
     // item; 2^13: three share one, and the hardware hands out the next
@@ -12,6 +13,12 @@ hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, con
     const uint32_t *ff = (const uint32_t*)f, *gg = (const uint32_t*)g;
     // the last step's sums over R transforms: |r| <= 0.502 m + R 2^20 has to stay below m
     const int mode = p.C.small ? 2 : p.C.m < (2200000u << (logn - 12));
+    if (crt) {
+        if (offs || logn != 13 || mode == 2) return hipErrorInvalidValue;
+        if (mode) hipLaunchKernelGGL((k_crt_wide<13, 1>), dim3(grid), dim3(256), 0, st, ff, gg, count, p, *crt);
+        else hipLaunchKernelGGL((k_crt_wide<13, 0>), dim3(grid), dim3(256), 0, st, ff, gg, count, p, *crt);
+        return hipGetLastError();
+    }
     switch (logn * 8 + (div ? 4 : 0) + mode) {
 #define CASE(n, mode)                                                                                                  \
     case n * 8 + mode:                                                                                                 \

@@ -128,25 +128,17 @@ __device__ __forceinline__ void cols_block(const uint32_t* src, uint32_t* dst, u
         for (int i = 0; i < 4; ++i) {
             uint32_t o[V];
 #pragma unroll
-            for (int s = 0; s < V; ++s) o[s] = KIND == INVERSE ? out_word<SMALL>(x[s][k][i], C) : (uint32_t)x[s][k][i];
+            for (int s = 0; s < V; ++s) o[s] = KIND == INVERSE && !CRT ? out_word<SMALL>(x[s][k][i], C) : (uint32_t)x[s][k][i];
             const uint32_t u1 = (uint32_t)(4 * gr + i);
             const uint32_t lo = KIND == TRANSFORM ? (u1 / S) * (16 * S * Q) + (u1 % S) * Q + V * (uint32_t)c : lw,
                            at = KIND == TRANSFORM ? S * Q * (4 * wave + k) + 16 * V * bx : at_word(k, i);
             if constexpr (CRT) {
                 const auto bh = wave_buf(crt.h, N * 8);
-                uint64_t r[V];
+                v2u r[V];
 #pragma unroll
-                for (int s = 0; s < V; ++s) {
-                    const int b = reduce_i((int)o[s] - (int)a1[k][i][s], C);   // (both below 2^24)
-                    const float q = __builtin_fmaf((float)b, crt.cq, MAGIC);
-                    const uint32_t t = canon_i((int32_t)mad24u(fbits(q), C.m, mad24s(b, crt.c, (uint32_t)C.it)), C);
-                    r[s] = a1[k][i][s] + (uint64_t)crt.m1 * t;
-                }
-                const v2u r0{(uint32_t)r[0], (uint32_t)(r[0] >> 32)};
-                if constexpr (V == 2)
-                    st_out4(bh, v4u{r0[0], r0[1], (uint32_t)r[1], (uint32_t)(r[1] >> 32)}, (lo + at) * 2);
-                else
-                    __builtin_amdgcn_raw_buffer_store_b64(r0, bh, lo * 8, at * 8, 0);
+                for (int s = 0; s < V; ++s) r[s] = combined<SMALL>(x[s][k][i], a1[k][i][s], crt, C);
+                if constexpr (V == 2) st_out4(bh, v4u{r[0][0], r[0][1], r[1][0], r[1][1]}, (lo + at) * 2);
+                else __builtin_amdgcn_raw_buffer_store_b64(r[0], bh, lo * 8, at * 8, 0);
             } else if constexpr (V == 2)
                 __builtin_amdgcn_raw_buffer_store_b64(v2u{o[0], o[1]}, bd, lo * 4, at * 4, 0);
             else st_out(bd, o[0], lo, at);

@@ -77,10 +77,20 @@ struct PointDiv {
     }
 };
 
+// The combining store's word for the tight residue r of the launch's modulus.
+template <bool SMALL>
+__device__ __forceinline__ v2u combined(int r, uint32_t a1, const Combine& crt, const I8K& C) {
+    const int b = reduce_i((int)out_word<SMALL>(r, C) - (int)a1, C);   // (both below 2^24)
+    const float q = __builtin_fmaf((float)b, crt.cq, MAGIC);
+    const uint32_t t = canon_i((int32_t)mad24u(fbits(q), C.m, mad24s(b, crt.c, (uint32_t)C.it)), C);
+    const uint64_t h = a1 + (uint64_t)crt.m1 * t;
+    return v2u{(uint32_t)h, (uint32_t)(h >> 32)};
+}
+
 // ROWS (of tiny_block and mid_block): the row phase of a longer transform
 // (four.hpp).  f and g are an item's rows of digits in scratch; the rows'
 // convolutions, times the twiddles rtt (four words per lane, in the order of the
-// registers), go to h as digits.
+// registers), go to h as digits.  CRT: the combining store instead of h's.
 
 // ------------------------------------------------------------------ N <= 2^8
 // N = 16 B, B <= 16; a block of 256 consecutive elements (16 / B sequences) is
@@ -90,9 +100,10 @@ struct PointDiv {
 // [c: (s, p0) -> v0], times w^-(p0 v0), over (s, p0) with N^-1.
 constexpr int TINY_BLOCKS = 4;   // blocks per wave and pass (1024 elements)
 constexpr int TINY_ROUNDS = 4;   // passes per wave, at most
-template <int n, bool SMALL, bool ROWS, class Point>
+template <int n, bool SMALL, bool ROWS, class Point, bool CRT = false>
 __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words,
-                                           int rounds, const I8Plan& p, uint32_t bx, const v4i* rtt, const Point& point) {
+                                           int rounds, const I8Plan& p, uint32_t bx, const v4i* rtt, const Point& point,
+                                           const Combine& crt = Combine{}) {
     constexpr int B = (1 << n) / 16;
     const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
     const I8K C(p.C);
@@ -121,7 +132,17 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
     for (int r = 0; r < rounds; ++r) {
         const uint64_t at = first + r * step;
         if (at >= words) break;
-        const auto bh = wave_buf(h + at, (uint32_t)(words - at < CH ? words - at : CH) * 4);
+        const uint32_t bytes = (uint32_t)(words - at < CH ? words - at : CH) * 4;
+        const auto bh = CRT ? wave_buf(crt.h + at, 2 * bytes) : wave_buf(h + at, bytes);
+        uint32_t a1[TINY_BLOCKS][4];
+        if constexpr (CRT) {
+            const auto ba = wave_buf(crt.a1 + at, bytes);
+#pragma unroll
+            for (int b = 0; b < TINY_BLOCKS; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    a1[b][i] = __builtin_amdgcn_raw_buffer_load_b32(ba, lw * 4, (256 * b + 16 * i) * 4, 0);
+        }
         v4i x[TINY_BLOCKS], y[TINY_BLOCKS];
 #pragma unroll
         for (int b = 0; b < TINY_BLOCKS; ++b)
@@ -165,8 +186,12 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
             const Sums s = digit_sums<KEEP>(A4, x[b], ti);
             x[b] = ROWS ? fold4_w(s, tt[b], C) : fold4_tight(s, C);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                st_out(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), lw, 256 * b + 16 * i);
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (CRT)
+                    __builtin_amdgcn_raw_buffer_store_b64(combined<SMALL>(x[b][i], a1[b][i], crt, C), bh, lw * 8,
+                                                          (256 * b + 16 * i) * 8, 0);
+                else st_out(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), lw, 256 * b + 16 * i);
+            }
         }
     }
 }
@@ -180,6 +205,11 @@ template <int n, bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_div_tiny(
     const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, int rounds, I8Plan p, Quotient q) {
     tiny_block<n, SMALL, false>(f, g, h, words, rounds, p, blockIdx.x, nullptr, PointDiv(q));
+}
+template <int n>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_crt_tiny(
+    const uint32_t* f, const uint32_t* g, uint64_t words, int rounds, I8Plan p, Combine crt) {
+    tiny_block<n, false, false, PointMul, true>(f, g, nullptr, words, rounds, p, blockIdx.x, nullptr, PointMul{}, crt);
 }
 
 // ------------------------------------------------------------------ 2^9 .. 2^12
@@ -215,9 +245,10 @@ __device__ __forceinline__ void mid_get(const v4i* x, v4i (&v)[4], int wave, int
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = x[((4 * wave + k) * 16 + c) * 4 + (gr ^ (c >> 2))];
 }
-template <int n, bool SMALL, bool ROWS, class Point>
+template <int n, bool SMALL, bool ROWS, class Point, bool CRT = false>
 __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words,
-                                          const I8Plan& p, uint32_t bx, const v4i* rtt, v4i (*xch)[1024], const Point& point) {
+                                          const I8Plan& p, uint32_t bx, const v4i* rtt, v4i (*xch)[1024], const Point& point,
+                                          const Combine& crt = Combine{}) {
     constexpr int R1 = (1 << n) / 256, N = 1 << n;
     using T = MidTab;
     // xch: f, g, the inverse: two barriers
@@ -225,7 +256,8 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t at = (uint64_t)bx * 4096;
     const uint32_t bytes = (uint32_t)(words - at < 4096 ? words - at : 4096) * 4;
-    const auto bf = wave_buf(f + at, bytes), bg = wave_buf(g + at, bytes), bh = wave_buf(h + at, bytes);
+    const auto bf = wave_buf(f + at, bytes), bg = wave_buf(g + at, bytes),
+               bh = CRT ? wave_buf(crt.h + at, 2 * bytes) : wave_buf(h + at, bytes);
     const uint32_t lw = (uint32_t)(c + 16 * R1 * 4 * gr);
     auto at_word = [&](int k, int i) {
         return (uint32_t)(((4 * wave + k) / R1) * N + 16 * ((4 * wave + k) % R1) + 16 * R1 * i);
@@ -286,6 +318,14 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
 #pragma unroll
         for (int k = 0; k < 4; ++k) tt[k] = rtt[((uint64_t)bx * 16 + 4 * wave + k) * 64 + lane];
     }
+    uint32_t a1[4][4];
+    if constexpr (CRT) {
+        const auto ba = wave_buf(crt.a1 + at, bytes);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a1[k][i] = __builtin_amdgcn_raw_buffer_load_b32(ba, lw * 4, at_word(k, i) * 4, 0);
+    }
     __syncthreads();
     mid_get(xch[2], x, wave, gr, c);
 #pragma unroll
@@ -293,7 +333,12 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
         const Sums s = digit_sums<KEEP>(V, x[k], ti);
         x[k] = ROWS ? fold4_w(s, tt[k], C) : fold4_tight(s, C);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), lw, at_word(k, i));
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (CRT)
+                __builtin_amdgcn_raw_buffer_store_b64(combined<SMALL>(x[k][i], a1[k][i], crt, C), bh, lw * 8,
+                                                      at_word(k, i) * 8, 0);
+            else st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), lw, at_word(k, i));
+        }
     }
 }
 
@@ -308,6 +353,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words, I8Plan p, Quotient q) {
     __shared__ v4i xch[3][1024];
     mid_block<n, SMALL, false>(f, g, h, words, p, blockIdx.x, nullptr, xch, PointDiv(q));
+}
+template <int n>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_crt_mid(
+    const uint32_t* f, const uint32_t* g, uint64_t words, I8Plan p, Combine crt) {
+    __shared__ v4i xch[3][1024];
+    mid_block<n, false, false, PointMul, true>(f, g, nullptr, words, p, blockIdx.x, nullptr, xch, PointMul{}, crt);
 }
 
 // ------------------------------------------------------------------ transforms

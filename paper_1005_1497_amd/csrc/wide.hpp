@@ -109,9 +109,10 @@ __device__ __forceinline__ void wide_core(v4i (&x)[4], v4i (&y)[4], const WideM&
 }
 
 // MODE 0: no extra reductions, 1: of the results (m < R 2.2e6), 2: also before the products (small moduli)
-template <int n, int MODE, class Point>
+// CRT: the combining store instead of h's (items back to back).
+template <int n, int MODE, class Point, bool CRT = false>
 __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* offs,
-                                           uint32_t count, I8Plan p, const Point& point) {
+                                           uint32_t count, I8Plan p, const Point& point, const Combine& crt = Combine{}) {
     using G = WideG<n>;
     using T = WideTab;
     constexpr int R = G::R, PW = G::PW;
@@ -166,7 +167,19 @@ __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g,
     // the last step's outputs k, from (j, q)
     auto last = [&](const v4i (&a)[PW][R], uint32_t item, Mat (&A)[R]) {
         const Init ti = init_tight(C);
-        const auto bh = buf(h, item);
+        const uint64_t at = (uint64_t)item * G::N;
+        const auto bh = CRT ? wave_buf(crt.h + at, G::N * 8) : buf(h, item);
+        uint32_t a1[CRT ? R : 1][PW][4];
+        if constexpr (CRT) {
+            const auto ba = wave_buf(crt.a1 + at, G::N * 4);
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+#pragma unroll
+                for (int q = 0; q < PW; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        a1[k][q][i] = __builtin_amdgcn_raw_buffer_load_b32(ba, lw * 4, at_word(q, k, i) * 4, 0);
+        }
 #pragma unroll
         for (int k = 0; k < R; ++k) {
             Mat B[R];
@@ -179,7 +192,12 @@ __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g,
             for (int q = 0; q < PW; ++q) {
                 const v4i r = fold4_tight(sums(A, a[q], ti), C);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) st_out(bh, out_word<MODE != 0>(r[i], C), lw, at_word(q, k, i));
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (CRT)
+                        __builtin_amdgcn_raw_buffer_store_b64(combined<MODE != 0>(r[i], a1[k][q][i], crt, C), bh, lw * 8,
+                                                              at_word(q, k, i) * 8, 0);
+                    else st_out(bh, out_word<MODE != 0>(r[i], C), lw, at_word(q, k, i));
+                }
             }
             if (k + 1 < R)
 #pragma unroll
@@ -296,6 +314,12 @@ __global__ __launch_bounds__(64 * WideG<n>::WAVES) __attribute__((amdgpu_waves_p
     const uint32_t* f, const uint32_t* g, uint32_t* h, const uint64_t* __restrict__ offs, uint32_t count, I8Plan p,
     Quotient q) {
     wide_block<n, MODE>(f, g, h, offs, count, p, PointDiv(q));
+}
+
+template <int n, int MODE>
+__global__ __launch_bounds__(64 * WideG<n>::WAVES) __attribute__((amdgpu_waves_per_eu(n == 13 ? 3 : 2, n == 13 ? 3 : 2))) void
+k_crt_wide(const uint32_t* f, const uint32_t* g, uint32_t count, I8Plan p, Combine crt) {
+    wide_block<n, MODE, PointMul, true>(f, g, nullptr, nullptr, count, p, PointMul{}, crt);
 }
 
 }  // namespace nttmi

@@ -323,3 +323,21 @@ def test_uneven_lengths_apart(nt, m, lo, hi, count):
         idx = np.unique(np.r_[0, N - 1, rng.integers(0, N, 10)]).astype(np.uint64)
         ref = oracle.conv_entries(f[o:o + N] % m, g[o:o + N] % m, m, idx)
         assert np.array_equal(outs[0][o:o + N][idx.astype(int)], ref.astype(np.uint32))
+
+
+@pytest.mark.parametrize("n", range(5, 14))
+def test_crt_short_lengths(nt, n):
+    """Integer convolutions whose combining store is that of the short kernels: one
+    item, and a chunk of 4096 elements with a part of the next; operands at the top of the
+    exact range in the last item."""
+    N = 1 << n
+    b = (46 - n) // 2
+    for rows in (1, max(2, 4096 // N + 1)):
+        rng = np.random.default_rng(8000 + 10 * n + rows)
+        f = rng.integers(0, 1 << b, (rows, N), dtype=np.uint32)
+        g = rng.integers(0, 1 << b, (rows, N), dtype=np.uint32)
+        f[-1] = g[-1] = (1 << b) - 1
+        h = host(nt.conv_crt(dev(f), dev(g))).reshape(rows, N)
+        assert np.all(h[-1] == N * ((1 << b) - 1) ** 2)
+        for r in {0, rows // 2}:
+            assert np.array_equal(h[r], oracle.conv_integer(f[r], g[r])), (rows, r)
