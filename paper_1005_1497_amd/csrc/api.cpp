@@ -615,7 +615,7 @@ ntt_status ntt_rows(const Plan* p, uint32_t elem_bits, uint32_t log2n, bool inv,
     hipStream_t s = (hipStream_t)stream;
     count(NTT_COUNT_TRANSFORM);
     if (elem_bits == 32 && p->i8.tab && (int)log2n <= WAVE_MAX_LOG2N)
-        return hip_status(launch_ntt_wave((int)log2n, inv, x, X, batch, p->i8, (uint32_t)cu_count(), s));
+        return hip_status(launch_ntt_wave((int)log2n, inv, x, X, batch, p->i8, s));
     if ((int)log2n <= SMALL_MAX_LOG2N)
         return hip_status(launch_ntt_small((int)elem_bits, log2n, inv, x, X, batch, p->dev, s));
     const size_t wb = elem_bits / 8;

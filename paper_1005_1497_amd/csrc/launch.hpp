@@ -95,8 +95,7 @@ hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uin
                             uint32_t cus, hipStream_t st, const Quotient* div = nullptr, const Combine* crt = nullptr);
 // Forward or inverse transforms of `batch` rows of length 2^logn (WAVE_MIN_LOG2N
 // .. WAVE_MAX_LOG2N) of 32-bit words back to back, natural order.
-hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& p, uint32_t cus,
-                           hipStream_t st);
+hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& p, hipStream_t st);
 // The same for lengths WIDE_MIN_LOG2N and WIDE_MAX_LOG2N, a workgroup per item:
 // items at offs[i], or back to back (offs null), on at most `cus` workgroups of
 // 2^14 at a time.

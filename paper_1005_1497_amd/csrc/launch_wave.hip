@@ -69,8 +69,7 @@ hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uin
     return hipGetLastError();
 }
 
-hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& pl, uint32_t cus,
-                           hipStream_t st) {
+hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& pl, hipStream_t st) {
     if (batch == 0) return hipSuccess;
     const uint64_t words = (uint64_t)batch << logn;
     const uint32_t* xx = (const uint32_t*)x;
@@ -78,17 +77,16 @@ hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t 
     I8Plan p = pl;
     if (!inv) p.tab = pl.fwd;
     p.C = make_i8c(p.C.m, 16);   // (the correction for raw words: a first step of radix 16)
-    const int rounds = tiny_rounds(words, cus);
-    const uint64_t share = 4ull * rounds * 256 * TINY_BLOCKS;
-    const dim3 tiny((uint32_t)((words + share - 1) / share)), mid((uint32_t)((words + 4095) / 4096)), wg(256);
+    const dim3 chunks((uint32_t)((words + 4095) / 4096)), wg(256);   // of 4096 elements
     switch (logn * 2 + (p.C.small ? 1 : 0)) {
-#define TINY(n, s)                                                                          \
-    case n * 2 + s:                                                                         \
-        hipLaunchKernelGGL((k_ntt_tiny<n, s>), tiny, wg, 0, st, xx, hh, words, rounds, p);  \
+#define TINY(n, s)                                                                                             \
+    case n * 2 + s:                                                                                            \
+        hipLaunchKernelGGL((k_ntt_tiny<n, s>), chunks, wg, 0, st, xx, hh, words, p);                           \
         break;
-#define MID(n, s)                                                                           \
-    case n * 2 + s:                                                                         \
-        hipLaunchKernelGGL((k_ntt_mid<n, s>), mid, wg, 0, st, xx, hh, words, p);            \
+#define MID(n, s)                                                                                              \
+    case n * 2 + s:                                                                                            \
+        if (words > (1u << 24)) hipLaunchKernelGGL((k_ntt_mid<n, s, 5>), chunks, wg, 0, st, xx, hh, words, p); \
+        else hipLaunchKernelGGL((k_ntt_mid<n, s, 4>), chunks, wg, 0, st, xx, hh, words, p);                    \
         break;
 #define BOTH(K, n) K(n, 0) K(n, 1)
         BOTH(TINY, 5) BOTH(TINY, 6) BOTH(TINY, 7) BOTH(TINY, 8) BOTH(MID, 9) BOTH(MID, 10) BOTH(MID, 11) BOTH(MID, 12)

@@ -368,60 +368,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 // forward one, because the short pieces lie on the side of the loads (2^26 elements
 // of 2^6: 105 us, the forward half 139; of 2^10: 128 and 188).  Bound by memory from
 // 2^24 elements on (2^26, against the LDS kernel's fp64 butterflies: 2^5 241 -> 145 us,
-// 2^8 102 -> 103, 2^12 150 -> 136; 2^24 elements of 2^10 36 -> 25, of 2^12 39 -> 26).
-// N <= 2^8: inputs p0 + B p', register element p', column (s, p0).
+// 2^8 103 -> 97, 2^9 124 -> 117; 2^24 elements of 2^8 25 -> 22, of 2^10 36 -> 26, of 2^12 40 -> 27).
+// N <= 2^8: inputs p0 + B p', register element p', column (s, p0).  One pass per wave:
+// beyond the memory-side cache several passes with the next one's words loaded ahead
+// are slower (2^25.3 elements of 2^8 60 against 64 us).
 template <int n, bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ntt_tiny(const uint32_t* f,
                                                                                             uint32_t* h, uint64_t words,
-                                                                                            int rounds, I8Plan p) {
+                                                                                            I8Plan p) {
     constexpr int B = (1 << n) / 16;
+    constexpr uint32_t CH = 256 * TINY_BLOCKS;
     const int lane = threadIdx.x & 63, gr = lane >> 4, c = lane & 15;
+    const uint64_t at = ((uint64_t)blockIdx.x * 4 + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * CH;
+    if (at >= words) return;
+    const uint32_t bytes = (uint32_t)(words - at < CH ? words - at : CH) * 4;
+    const auto bf = wave_buf(f + at, bytes), bh = wave_buf(h + at, bytes);
+    const uint32_t li = (uint32_t)((c / B) * 16 * B + c % B + 4 * B * gr), lo = (uint32_t)(c + 64 * gr);
+    v4i x[TINY_BLOCKS];
+#pragma unroll
+    for (int b = 0; b < TINY_BLOCKS; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[b][i] = ld_raw(bf, li, 256 * b + B * i);
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat A1 = ld_mat(t + 384, lane), A2 = ld_mat(t + 576, lane);
     const Tw T1 = ld_tw(t + 768 + 128, lane);
     const Init ti = init_tight(C), raw = init_raw(ti, C, [&](int) { return c == 0; });
-    const uint32_t li = (uint32_t)((c / B) * 16 * B + c % B + 4 * B * gr), lo = (uint32_t)(c + 64 * gr);
-    constexpr uint32_t CH = 256 * TINY_BLOCKS;
-    int nx[TINY_BLOCKS][4];   // the next blocks' words, loaded ahead
-    auto load = [&](uint64_t at) {
-        const uint64_t a = at < words ? at : 0;
-        const auto bu = wave_buf(f + a, at < words ? (uint32_t)(words - a < CH ? words - a : CH) * 4 : 0u);
 #pragma unroll
-        for (int b = 0; b < TINY_BLOCKS; ++b)
+    for (int b = 0; b < TINY_BLOCKS; ++b) {
+        x[b] = fold4_tw(digit_sums<TURN>(A1, x[b], raw), T1, C);
+        x[b] = fold4_tight(digit_sums<KEEP>(A2, x[b], ti), C);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                nx[b][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(bu, li * 4, (256 * b + B * i) * 4, 0);
-    };
-    const uint64_t first = (uint64_t)blockIdx.x * (4 * CH) * rounds +
-                           (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * CH;
-    load(first);
-    for (int r = 0; r < rounds; ++r) {
-        const uint64_t at = first + (uint64_t)r * (4 * CH);
-        if (at >= words) break;
-        const auto bh = wave_buf(h + at, (uint32_t)(words - at < CH ? words - at : CH) * 4);
-        v4i x[TINY_BLOCKS];
-#pragma unroll
-        for (int b = 0; b < TINY_BLOCKS; ++b)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) x[b][i] = nx[b][i] ^ (int)DIG;
-        __builtin_amdgcn_sched_barrier(0);
-        if (r + 1 < rounds) load(at + 4 * CH);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int b = 0; b < TINY_BLOCKS; ++b) {
-            x[b] = fold4_tw(digit_sums<TURN>(A1, x[b], raw), T1, C);
-            x[b] = fold4_tight(digit_sums<KEEP>(A2, x[b], ti), C);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) st_out(bh, out_word<SMALL>(x[b][i], C), lo, 256 * b + 16 * i);
-        }
+        for (int i = 0; i < 4; ++i) st_out(bh, out_word<SMALL>(x[b][i], C), lo, 256 * b + 16 * i);
     }
 }
 
 // 2^9 .. 2^12: inputs p0 + 16 (p1 + R1 p2) with p0 in the registers: 16 consecutive
-// bytes per lane, and a row of 64 in the four waves.
-template <int n, bool SMALL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ntt_mid(const uint32_t* f,
+// bytes per lane, and a row of 64 in the four waves.  WAVES per SIMD: four, or five
+// from more than 2^24 elements on, which no longer lie in the memory-side cache (2^25.3
+// of 2^9 82 -> 76 us, 2^26 129 -> 120; 2^24 26.2 -> 27.2, one row of 2^12 3.9 -> 4.4).
+template <int n, bool SMALL, int WAVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) void k_ntt_mid(const uint32_t* f,
                                                                                            uint32_t* h, uint64_t words,
                                                                                            I8Plan p) {
     constexpr int R1 = (1 << n) / 256, N = 1 << n;

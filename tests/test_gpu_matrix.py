@@ -341,3 +341,16 @@ def test_crt_short_lengths(nt, n):
         assert np.all(h[-1] == N * ((1 << b) - 1) ** 2)
         for r in {0, rows // 2}:
             assert np.array_equal(h[r], oracle.conv_integer(f[r], g[r])), (rows, r)
+
+
+@pytest.mark.parametrize("n", [9, 12])
+def test_transforms_beyond_the_cache(nt, n):
+    """The first and the last row of a transform of more than 2^24 elements (another
+    number of waves per SIMD) against the same rows by themselves."""
+    m, N = 13631489, 1 << n
+    rows = ((1 << 24) >> n) + 1
+    x = torch.randint(0, m, (rows, N), dtype=torch.int32, device="cuda")
+    for fn in (nt.ntt_forward, nt.ntt_inverse):
+        X = fn(x, m)
+        for r in (0, rows - 1):
+            assert torch.equal(X[r], fn(x[r:r + 1].contiguous(), m)[0])
