@@ -90,7 +90,7 @@ hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, 
 // The wave kernels (matrix cores): `count` convolutions of length 2^logn
 // (WAVE_MIN_LOG2N .. WAVE_MAX_LOG2N) of 32-bit words back to back.
 // div: the quotients g / f instead (exact deconvolutions); crt: the combining store (h
-// unused; moduli from 2^21 on; of the next launcher 2^13 alone).
+// unused; moduli from 2^21 on; in the next launcher 2^13 alone and from 4,400,000 on).
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
                             uint32_t cus, hipStream_t st, const Quotient* div = nullptr, const Combine* crt = nullptr);
 // Forward or inverse transforms of `batch` rows of length 2^logn (WAVE_MIN_LOG2N

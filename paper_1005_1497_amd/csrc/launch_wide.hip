@@ -14,9 +14,8 @@ hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, con
     // the last step's sums over R transforms: |r| <= 0.502 m + R 2^20 has to stay below m
     const int mode = p.C.small ? 2 : p.C.m < (2200000u << (logn - 12));
     if (crt) {
-        if (offs || logn != 13 || mode == 2) return hipErrorInvalidValue;
-        if (mode) hipLaunchKernelGGL((k_crt_wide<13, 1>), dim3(grid), dim3(256), 0, st, ff, gg, count, p, *crt);
-        else hipLaunchKernelGGL((k_crt_wide<13, 0>), dim3(grid), dim3(256), 0, st, ff, gg, count, p, *crt);
+        if (offs || logn != 13 || mode) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_crt_wide, dim3(grid), dim3(256), 0, st, ff, gg, count, p, *crt);
         return hipGetLastError();
     }
     switch (logn * 8 + (div ? 4 : 0) + mode) {

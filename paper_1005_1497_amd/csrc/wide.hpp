@@ -316,10 +316,9 @@ __global__ __launch_bounds__(64 * WideG<n>::WAVES) __attribute__((amdgpu_waves_p
     wide_block<n, MODE>(f, g, h, offs, count, p, PointDiv(q));
 }
 
-template <int n, int MODE>
-__global__ __launch_bounds__(64 * WideG<n>::WAVES) __attribute__((amdgpu_waves_per_eu(n == 13 ? 3 : 2, n == 13 ? 3 : 2))) void
-k_crt_wide(const uint32_t* f, const uint32_t* g, uint32_t count, I8Plan p, Combine crt) {
-    wide_block<n, MODE, PointMul, true>(f, g, nullptr, nullptr, count, p, PointMul{}, crt);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_crt_wide(
+    const uint32_t* f, const uint32_t* g, uint32_t count, I8Plan p, Combine crt) {
+    wide_block<13, 0, PointMul, true>(f, g, nullptr, nullptr, count, p, PointMul{}, crt);
 }
 
 }  // namespace nttmi
