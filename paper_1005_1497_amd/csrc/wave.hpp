@@ -11,8 +11,11 @@
 
 namespace nttmi {
 
-// A wave's buffer over `bytes` valid bytes (loads beyond read 0, stores beyond
-// are dropped).
+// A wave's buffer over `bytes` valid bytes: loads beyond read 0 and stores beyond are
+// dropped, by a check that covers the lane's offset and the instruction's constant but not
+// a scalar offset.  Where a chunk may be a part of one, all of the offset is therefore in
+// those two: the accessors below take the lane's word and a constant one (up to 1023 words
+// it is in the instruction itself).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buf(const void* p, uint32_t bytes) {
     // (uniform by construction; said so, or the descriptor would be taken lane by lane)
     const uint64_t a = (uint64_t)(uintptr_t)p;
@@ -21,11 +24,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buf(const void* p, uint32
     return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), (short)0,
                                              __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
+__device__ __forceinline__ uint32_t ld_word(__amdgpu_buffer_rsrc_t b, uint32_t lane_word, uint32_t word) {
+    return __builtin_amdgcn_raw_buffer_load_b32(b, (lane_word + word) * 4, 0, 0);
+}
 __device__ __forceinline__ int ld_raw(__amdgpu_buffer_rsrc_t b, uint32_t lane_word, uint32_t word) {
-    return (int)(__builtin_amdgcn_raw_buffer_load_b32(b, lane_word * 4, word * 4, 0) ^ DIG);
+    return (int)(ld_word(b, lane_word, word) ^ DIG);
 }
 __device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uint32_t lane_word, uint32_t word) {
-    __builtin_amdgcn_raw_buffer_store_b32(x, b, lane_word * 4, word * 4, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(x, b, (lane_word + word) * 4, 0, 0);
+}
+__device__ __forceinline__ void st_out2(__amdgpu_buffer_rsrc_t b, v2u x, uint32_t lane_word, uint32_t word) {
+    __builtin_amdgcn_raw_buffer_store_b64(x, b, (lane_word + word) * 8, 0, 0);
 }
 // Sixteen bytes at once.  With a scalar register as offset the compiler would leave no
 // wait before the next write to the stored registers, and the last lanes of the store
@@ -121,7 +130,7 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
         for (int b = 0; b < TINY_BLOCKS; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                v[b][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(bu, lw * 4, (256 * b + 16 * i) * 4, 0);
+                v[b][i] = (int)ld_word(bu, lw, 256 * b + 16 * i);
     };
     // a workgroup's passes lie together
     const uint64_t first = (uint64_t)bx * (4 * CH) * rounds +
@@ -134,15 +143,6 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
         if (at >= words) break;
         const uint32_t bytes = (uint32_t)(words - at < CH ? words - at : CH) * 4;
         const auto bh = CRT ? wave_buf(crt.h + at, 2 * bytes) : wave_buf(h + at, bytes);
-        uint32_t a1[TINY_BLOCKS][4];
-        if constexpr (CRT) {
-            const auto ba = wave_buf(crt.a1 + at, bytes);
-#pragma unroll
-            for (int b = 0; b < TINY_BLOCKS; ++b)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    a1[b][i] = __builtin_amdgcn_raw_buffer_load_b32(ba, lw * 4, (256 * b + 16 * i) * 4, 0);
-        }
         v4i x[TINY_BLOCKS], y[TINY_BLOCKS];
 #pragma unroll
         for (int b = 0; b < TINY_BLOCKS; ++b)
@@ -182,14 +182,18 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
                 forward(b);
                 x[b] = mul4_fg<SMALL>(x[b], y[b], C);
             }
+            uint32_t a1[4];   // (here: loaded before the transforms they spilled 11 registers)
+            if constexpr (CRT) {
+                const auto ba = wave_buf(crt.a1 + at, bytes);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a1[i] = ld_word(ba, lw, 256 * b + 16 * i);
+            }
             x[b] = fold4_tw(digit_sums<TURN>(A3, x[b], ti), T2, C);
             const Sums s = digit_sums<KEEP>(A4, x[b], ti);
             x[b] = ROWS ? fold4_w(s, tt[b], C) : fold4_tight(s, C);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (CRT)
-                    __builtin_amdgcn_raw_buffer_store_b64(combined<SMALL>(x[b][i], a1[b][i], crt, C), bh, lw * 8,
-                                                          (256 * b + 16 * i) * 8, 0);
+                if constexpr (CRT) st_out2(bh, combined<SMALL>(x[b][i], a1[i], crt, C), lw, 256 * b + 16 * i);
                 else st_out(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), lw, 256 * b + 16 * i);
             }
         }
@@ -245,6 +249,13 @@ __device__ __forceinline__ void mid_get(const v4i* x, v4i (&v)[4], int wave, int
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = x[((4 * wave + k) * 16 + c) * 4 + (gr ^ (c >> 2))];
 }
+// First word of register r's element i in lane 0; a sum, mid_word(4 w + k, i) =
+// mid_word(4 w, 0) + mid_word(k, i) for k < 4: the wave's part goes to the lane's offset.
+template <int n>
+__device__ constexpr uint32_t mid_word(int r, int i) {
+    constexpr int R1 = (1 << n) / 256;
+    return (uint32_t)((r / R1) * (1 << n) + 16 * (r % R1) + 16 * R1 * i);
+}
 template <int n, bool SMALL, bool ROWS, class Point, bool CRT = false>
 __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, uint32_t* h, uint64_t words,
                                           const I8Plan& p, uint32_t bx, const v4i* rtt, v4i (*xch)[1024], const Point& point,
@@ -258,19 +269,16 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
     const uint32_t bytes = (uint32_t)(words - at < 4096 ? words - at : 4096) * 4;
     const auto bf = wave_buf(f + at, bytes), bg = wave_buf(g + at, bytes),
                bh = CRT ? wave_buf(crt.h + at, 2 * bytes) : wave_buf(h + at, bytes);
-    const uint32_t lw = (uint32_t)(c + 16 * R1 * 4 * gr);
-    auto at_word = [&](int k, int i) {
-        return (uint32_t)(((4 * wave + k) / R1) * N + 16 * ((4 * wave + k) % R1) + 16 * R1 * i);
-    };
+    const uint32_t lw = (uint32_t)(c + 16 * R1 * 4 * gr) + mid_word<n>(4 * wave, 0);
     v4i x[4], y[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bf, lw, at_word(k, i)) ^ (ROWS ? (int)DIG : 0);
+        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bf, lw, mid_word<n>(k, i)) ^ (ROWS ? (int)DIG : 0);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y[k][i] = ld_raw(bg, lw, at_word(k, i)) ^ (ROWS ? (int)DIG : 0);
+        for (int i = 0; i < 4; ++i) y[k][i] = ld_raw(bg, lw, mid_word<n>(k, i)) ^ (ROWS ? (int)DIG : 0);
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat W = ld_mat(t + T::W, lane);
@@ -324,7 +332,7 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a1[k][i] = __builtin_amdgcn_raw_buffer_load_b32(ba, lw * 4, at_word(k, i) * 4, 0);
+            for (int i = 0; i < 4; ++i) a1[k][i] = ld_word(ba, lw, mid_word<n>(k, i));
     }
     __syncthreads();
     mid_get(xch[2], x, wave, gr, c);
@@ -334,10 +342,8 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
         x[k] = ROWS ? fold4_w(s, tt[k], C) : fold4_tight(s, C);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if constexpr (CRT)
-                __builtin_amdgcn_raw_buffer_store_b64(combined<SMALL>(x[k][i], a1[k][i], crt, C), bh, lw * 8,
-                                                      at_word(k, i) * 8, 0);
-            else st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), lw, at_word(k, i));
+            if constexpr (CRT) st_out2(bh, combined<SMALL>(x[k][i], a1[k][i], crt, C), lw, mid_word<n>(k, i));
+            else st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), lw, mid_word<n>(k, i));
         }
     }
 }
@@ -419,11 +425,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVE
     const uint64_t at = (uint64_t)blockIdx.x * 4096;
     const uint32_t bytes = (uint32_t)(words - at < 4096 ? words - at : 4096) * 4;
     const auto bf = wave_buf(f + at, bytes), bh = wave_buf(h + at, bytes);
-    const uint32_t li = (uint32_t)((c / R1) * N + 16 * (c % R1) + 16 * R1 * 4 * gr);
+    const uint32_t li = (uint32_t)((c / R1) * N + 16 * (c % R1) + 16 * R1 * 4 * gr + 4 * wave),
+                   lo = (uint32_t)(c + 16 * R1 * 4 * gr) + mid_word<n>(4 * wave, 0);
     v4i x[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b128(bf, li * 4, (4 * wave + 16 * R1 * i) * 4, 0);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(bf, (li + 16 * R1 * i) * 4, 0, 0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) x[k][i] = (int)(v[k] ^ DIG);
     }
@@ -435,11 +442,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVE
 #pragma unroll
     for (int k = 0; k < 4; ++k) tw[k] = ld_tw(t + T::TB + (4 * wave + k) * 128, lane);
     const Init ti = init_tight(C), raw = init_raw(ti, C, [&](int) { return c == 0; });
+    // (two loops: with both steps in one, five waves per SIMD spilled up to 12 registers)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        x[k] = fold4_tw(digit_sums<TURN>(V, x[k], raw), tk, C);
-        x[k] = fold4_tw(digit_sums<KEEP>(U, x[k], ti), tw[k], C);
-    }
+    for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<TURN>(V, x[k], raw), tk, C);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<KEEP>(U, x[k], ti), tw[k], C);
     mid_put(xch, x, wave, gr, c);
     __syncthreads();
     mid_get(xch, x, wave, gr, c);
@@ -447,9 +454,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVE
     for (int k = 0; k < 4; ++k) {
         x[k] = fold4_tight(digit_sums<KEEP>(V, x[k], ti), C);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            st_out(bh, out_word<SMALL>(x[k][i], C), (uint32_t)(c + 16 * R1 * 4 * gr),
-                   (uint32_t)(((4 * wave + k) / R1) * N + 16 * ((4 * wave + k) % R1) + 16 * R1 * i));
+        for (int i = 0; i < 4; ++i) st_out(bh, out_word<SMALL>(x[k][i], C), lo, mid_word<n>(k, i));
     }
 }
 
