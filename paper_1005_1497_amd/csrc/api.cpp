@@ -201,6 +201,23 @@ hipError_t upload(T** d, const std::vector<T>& h) {
     return e;
 }
 
+// Compute units of a device (0 unknown), with the cache lock held.
+int cu_count_locked(int dev) {
+    auto it = caches().cu_count.find(dev);
+    if (it != caches().cu_count.end()) return it->second;
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 0;
+    caches().cu_count[dev] = n;
+    return n;
+}
+
+int cu_count() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    std::lock_guard<std::mutex> g(caches().mu);
+    return cu_count_locked(dev);
+}
+
 // Device tables of the plan (m, N = 2^log2n, root): the powers root^e mod m,
 // e < N, which are the harmonics of the digital circle (Eq. 5) generated one
 // factor at a time, and for four-step lengths the twiddles root^(+-t1 u2).
@@ -219,6 +236,7 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
         *out = &it->second;
         return NTT_OK;
     }
+    (void)cu_count_locked(dev);   // known from here on: a call that may not allocate asks for it
     const uint64_t N = 1ull << log2n;
     std::vector<double2> hP(N);
     uint64_t x = 1 % m;
@@ -509,22 +527,6 @@ ntt_status get_desc(const std::vector<uint64_t>& h, bool transient, void* stream
     out->ptr = (const uint64_t*)sl.dev;
     count(NTT_COUNT_DESC_RING);
     return NTT_OK;
-}
-
-int cu_count() {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    Caches& c = caches();
-    {
-        std::lock_guard<std::mutex> g(c.mu);
-        auto it = c.cu_count.find(dev);
-        if (it != c.cu_count.end()) return it->second;
-    }
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 0;
-    std::lock_guard<std::mutex> g(c.mu);
-    c.cu_count[dev] = n;
-    return n;
 }
 
 // [a, a+na) and [b, b+nb) in bytes: 0 disjoint, 1 identical start and size, 2 partial
