@@ -350,18 +350,28 @@ void ntt_server_destroy(ntt_server *srv);
  * and threads), of the launches it has made by form and of its descriptor
  * uploads.  Writes counts[k] for k < min(n, NTT_COUNT_SLOTS); counts is a
  * host array owned by the caller.  Lets a caller (the tests) see which form
- * a call actually took: read before and after the call and compare. */
+ * a call actually took: read before and after the call and compare.  The first
+ * five say what the work was, whichever kernels ran it; the MATRIX ones count
+ * those of these launches that ran the matrix-core kernels (32-bit words, m up to
+ * 14,600,000), so that a class without one ran the fp64 kernels.  (The columns of
+ * conv2d_circular count as convolutions where they run as such.) */
 enum {
-    NTT_COUNT_SMALL = 0,         /* LDS convolution kernels (N <= 2^12) */
+    NTT_COUNT_SMALL = 0,         /* convolutions up to 2^12 (one per launch) */
     NTT_COUNT_FOURSTEP = 1,      /* few items above 2^12, each spread over the chip (one per launch sequence) */
-    NTT_COUNT_FUSED = 2,         /* many items of one length above 2^12 (one per launch sequence) */
+    NTT_COUNT_FUSED = 2,         /* many items of one length above 2^12, and every quotient and combining
+                                    convolution above 2^12 (one per launch sequence) */
     NTT_COUNT_MULTI = 3,         /* batches of several lengths as one (one per launch sequence) */
     NTT_COUNT_TRANSFORM = 4,     /* transform launch sequences (ntt_forward / ntt_inverse rows) */
     NTT_COUNT_DESC_CACHED = 5,   /* descriptors uploaded into the content-addressed cache */
     NTT_COUNT_DESC_RING = 6,     /* descriptors uploaded through a stream's staging ring */
     NTT_COUNT_DESC_EVICTED = 7,  /* cache entries freed when the cache was full */
     NTT_COUNT_QUEUE_CREATED = 8, /* per-stream work queues created */
-    NTT_COUNT_SLOTS = 9
+    NTT_COUNT_MATRIX_SHORT = 9,      /* matrix cores: convolutions and quotients up to 2^12 */
+    NTT_COUNT_MATRIX_ONE = 10,       /* matrix cores: 2^13 and 2^14, an item in one workgroup */
+    NTT_COUNT_MATRIX_THREE = 11,     /* matrix cores: 2^13 .. 2^19 in three launches (one per sequence; a MULTI
+                                        batch may send several, a ONE batch of 2^14 one for its last items) */
+    NTT_COUNT_MATRIX_TRANSFORM = 12, /* matrix cores: transform launch sequences */
+    NTT_COUNT_SLOTS = 13
 };
 void ntt_launch_counts(uint64_t *counts, uint32_t n);
 

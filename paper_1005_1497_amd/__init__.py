@@ -392,7 +392,7 @@ def conv_batched(f: torch.Tensor, g: torch.Tensor, desc, m: int, root: int = 2, 
 
 
 COUNT_NAMES = ("small", "fourstep", "fused", "multi", "transform", "desc_cached", "desc_ring", "desc_evicted",
-               "queue_created")
+               "queue_created", "matrix_short", "matrix_one", "matrix_three", "matrix_transform")
 
 
 def launch_counts() -> dict:

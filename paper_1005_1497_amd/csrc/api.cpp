@@ -583,6 +583,7 @@ ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const
     void* ws = nullptr;
     const ntt_status st = get_buf(caches().work, stream, (size_t)group * 8 << n, &ws);
     if (st != NTT_OK) return st;
+    count(NTT_COUNT_MATRIX_THREE);
     return hip_status(launch_conv_four((int)n, f, g, h, doffs, c, group, ws, p->trans, p->four, s, div, crt));
 }
 
@@ -591,12 +592,15 @@ ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f
     hipStream_t s = (hipStream_t)stream;
     if ((int)log2n <= SMALL_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
-        if (wbits == 32 && p->i8.tab)
+        if (wbits == 32 && p->i8.tab) {
+            count(NTT_COUNT_MATRIX_SHORT);
             return hip_status(launch_conv_wave((int)log2n, f, g, h, 1, p->i8, (uint32_t)cu_count(), s));
+        }
         return hip_status(launch_conv_small((int)wbits, log2n, f, g, h, nullptr, 1, p->dev, s));
     }
     if (use_wide(p, wbits, log2n, 1)) {
         count(NTT_COUNT_FOURSTEP);
+        count(NTT_COUNT_MATRIX_ONE);
         return hip_status(launch_conv_wide((int)log2n, f, g, h, nullptr, 1, (uint32_t)cu_count(), p->i8, s));
     }
     if (use_four(p, wbits, log2n, 1)) {
@@ -616,8 +620,10 @@ ntt_status ntt_rows(const Plan* p, uint32_t elem_bits, uint32_t log2n, bool inv,
                     uint32_t batch, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     count(NTT_COUNT_TRANSFORM);
-    if (elem_bits == 32 && p->i8.tab && (int)log2n <= WAVE_MAX_LOG2N)
+    if (elem_bits == 32 && p->i8.tab && (int)log2n <= WAVE_MAX_LOG2N) {
+        count(NTT_COUNT_MATRIX_TRANSFORM);
         return hip_status(launch_ntt_wave((int)log2n, inv, x, X, batch, p->i8, s));
+    }
     if ((int)log2n <= SMALL_MAX_LOG2N)
         return hip_status(launch_ntt_small((int)elem_bits, log2n, inv, x, X, batch, p->dev, s));
     const size_t wb = elem_bits / 8;
@@ -626,6 +632,7 @@ ntt_status ntt_rows(const Plan* p, uint32_t elem_bits, uint32_t log2n, bool inv,
     // memory-side cache: 2^26 elements of 2^16 in one chunk 280 us, 128 MiB of
     // scratch 262, 64 MiB 273)
     const bool trans = elem_bits == 32 && p->trans[inv].tab;
+    if (trans) count(NTT_COUNT_MATRIX_TRANSFORM);
     const uint64_t budget = trans ? 1ull << 27 : 1ull << 30;
     const uint32_t chunk = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, budget / per), 65535);
     void* ws = nullptr;
@@ -674,9 +681,11 @@ ntt_status launch_items(uint32_t n, uint32_t c, uint64_t base, const uint64_t* d
     ntt_status st = NTT_OK;
     if ((int)n <= SMALL_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
-        if (elem_bits == 32 && p->i8.tab && contiguous && form == CF_DEFAULT)
+        if (elem_bits == 32 && p->i8.tab && contiguous && form == CF_DEFAULT) {
+            count(NTT_COUNT_MATRIX_SHORT);
             return hip_status(launch_conv_wave((int)n, F + base * wb, G + base * wb, H + base * wb, c, p->i8,
                                                (uint32_t)cu_count(), s));
+        }
         return hip_status(launch_conv_small((int)elem_bits, n, F + base * wb, G + base * wb, H + base * wb, doffs, c,
                                             p->dev, s, form == CF_SMALL_WAVE ? SMALL_TILE_WAVE : SMALL_TILE_256));
     }
@@ -713,6 +722,7 @@ ntt_status launch_items(uint32_t n, uint32_t c, uint64_t base, const uint64_t* d
     // the matrix-core forms, counted by what the batch is: few items or many
     if (form == CF_DEFAULT && use_wide(p, elem_bits, n, c)) {
         count(few ? NTT_COUNT_FOURSTEP : NTT_COUNT_FUSED);
+        count(NTT_COUNT_MATRIX_ONE);
         // 2^14 goes round by round, an item to a CU; a last round of few items (up to a
         // fifth of the CUs) takes less time spread over the chip, 12 to 18 us against 22
         const uint32_t cus = (uint32_t)cu_count(), rest = n == 14 && c > cus && 5 * (c % cus) <= cus ? c % cus : 0;
@@ -846,6 +856,7 @@ ntt_status launch_multi(const std::map<uint32_t, std::vector<uint64_t>>& cls,
     for (const auto& o : own) {
         const uint32_t c = (uint32_t)cls.at(o.first).size();
         const Plan* p = plans[o.first];
+        count(NTT_COUNT_MATRIX_THREE);
         st = hip_status(launch_conv_four((int)o.first, F, G, H, dblob + o.second, c, four_group(o.first, c), ws, p->trans,
                                          p->four, s));
         if (st != NTT_OK) return st;
@@ -1088,16 +1099,20 @@ ntt_status conv_circular_noalloc(uint64_t m, uint32_t log2n, uint64_t root, uint
     hipStream_t s = (hipStream_t)stream;
     if (!fourstep) {
         count(NTT_COUNT_SMALL);
-        if (elem_bits == 32 && p->i8.tab)
+        if (elem_bits == 32 && p->i8.tab) {
+            count(NTT_COUNT_MATRIX_SHORT);
             return hip_status(launch_conv_wave((int)log2n, f, g, h, 1, p->i8, (uint32_t)cu_count(), s));
+        }
         return hip_status(launch_conv_small((int)elem_bits, log2n, f, g, h, nullptr, 1, p->dev, s));
     }
     void* ws = nullptr;
     const hipError_t e = noalloc_scratch(&ws);
     if (e != hipSuccess) return hip_status(e);
     count(NTT_COUNT_FOURSTEP);
-    if (use_four(p, elem_bits, log2n, 1))
+    if (use_four(p, elem_bits, log2n, 1)) {
+        count(NTT_COUNT_MATRIX_THREE);
         return hip_status(launch_conv_four((int)log2n, f, g, h, nullptr, 1, 1, ws, p->trans, p->four, s));
+    }
     return hip_status(launch_conv_fourstep((int)elem_bits, log2n, f, g, h, 1, 0, ws, p->dev, s, nullptr,
                                            (uint32_t)cu_count()));
 }
@@ -1138,9 +1153,11 @@ ntt_status conv_deconvolve(uint64_t m, uint32_t log2n, uint64_t root, uint32_t e
     const Quotient div{p->dev.M, (uint32_t*)flag};
     if (elem_bits == 32 && p->i8.tab && (int)log2n <= WAVE_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
+        count(NTT_COUNT_MATRIX_SHORT);
         e = launch_conv_wave((int)log2n, F, Hh, Gg, batch, p->i8, (uint32_t)cu_count(), s, &div);
     } else if (use_wide(p, elem_bits, log2n, batch)) {
         count(NTT_COUNT_FUSED);
+        count(NTT_COUNT_MATRIX_ONE);
         e = launch_conv_wide((int)log2n, F, Hh, Gg, nullptr, batch, (uint32_t)cu_count(), p->i8, s, &div);
     } else if (elem_bits == 32 && p->four.tab &&
                (((uint64_t)batch << log2n) <= (1u << 24) || 3ull * batch < 2ull * cu_count())) {
@@ -1148,7 +1165,7 @@ ntt_status conv_deconvolve(uint64_t m, uint32_t log2n, uint64_t root, uint32_t e
         // an item idle (100 of 2^18: 644 us, three launches 347; one of 2^19: 1373, 45; 400
         // of 2^15 up to 2^24 elements even); with every CU busy it is ahead where the
         // three launches wait for memory (1000 of 2^16: 638 against 722)
-        count(NTT_COUNT_FOURSTEP);
+        count(NTT_COUNT_FUSED);   // (the class of every quotient above 2^12)
         st = conv_four(p, log2n, batch, F, Hh, Gg, nullptr, s, stream, &div);
         if (st != NTT_OK) return st;
     } else if ((int)log2n <= SMALL_MAX_LOG2N) {
@@ -1224,14 +1241,16 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     const Combine crt{a1, (uint64_t*)h, (uint32_t)m1, cb, (float)(-(double)cb / (double)m2)};
     if ((int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WAVE_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
+        count(NTT_COUNT_MATRIX_SHORT);
         return hip_status(launch_conv_wave((int)log2n, f, g, nullptr, batch, p2->i8, (uint32_t)cu_count(), s, nullptr, &crt));
     }
     if (log2n == 13) {
         count(NTT_COUNT_FUSED);
+        count(NTT_COUNT_MATRIX_ONE);
         return hip_status(launch_conv_wide(13, f, g, nullptr, nullptr, batch, (uint32_t)cu_count(), p2->i8, s, nullptr, &crt));
     }
     if (log2n >= 14 && (use_four(p2, 32, log2n, batch) || 3ull * batch < 2 * grid)) {
-        count(NTT_COUNT_FOURSTEP);
+        count(NTT_COUNT_FUSED);   // (the class of every combining convolution above 2^12)
         return conv_four(p2, log2n, batch, f, g, nullptr, nullptr, s, stream, nullptr, &crt);
     }
     if (log2n >= 14) {
