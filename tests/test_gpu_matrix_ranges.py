@@ -1,0 +1,105 @@
+"""The matrix-core kernels (32-bit words) on both sides of the sizes and moduli where their
+launches change: several passes of a workgroup (2^5 .. 2^8), 32 columns to a workgroup
+instead of 16 and two passes of the row kernels (2^13 and longer), more rows than one chunk
+of scratch holds, and moduli below 2^21 at every length that one has.  Results are exact:
+equality with the oracle's sums for sampled rows and entries, with the same rows run by
+themselves, and of round trips for every word."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+M = 13631489
+# the longest length that each small prime has: 2^15, 2^16, 2^16, 2^17, 2^18
+SMALL = {163841: 15, 65537: 16, 1376257: 16, 1179649: 17, 786433: 18}
+WIDE_BLOCKS = 1536   # of 4096 elements: from here on 32 columns to a workgroup
+
+
+@pytest.fixture(scope="module")
+def nt():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256   # the counts below are for as many
+    import paper_1005_1497_amd as nt
+    return nt
+
+
+def words(seed, *shape):
+    """Random 32-bit words, all of them (operands need not be reduced)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return torch.randint(-(1 << 31), 1 << 31, shape, generator=gen, dtype=torch.int64, device="cuda").to(torch.int32)
+
+
+def reduced(x, m):
+    return ((x.to(torch.int64) & 0xFFFFFFFF) % m).to(torch.int32)
+
+
+def batch(nt, f, g, n, m, offs=None, flags=0):
+    order = nt.max_log2n(m)
+    count = f.numel() >> n
+    offs = np.arange(count, dtype=np.int64) << n if offs is None else offs
+    out = nt.conv_batched(f.view(-1), g.view(-1), nt.BatchDesc(np.full(count, n), offs), m,
+                          root=nt.euler_root(m, order), root_log2order=order, flags=nt.FLAG_EULER | flags)
+    return out.view(f.shape)
+
+
+def check_convolutions(h, f, g, m, items):
+    n, rng = f.shape[1].bit_length() - 1, np.random.default_rng(7)
+    N = 1 << n
+    for i in items:
+        a, b, c = host(f[i]) % np.uint32(m), host(g[i]) % np.uint32(m), host(h[i])
+        idx = np.arange(N, dtype=np.uint64) if n <= 9 else \
+            np.concatenate([[0, 1, 255, 256, N // 2, N - 1], rng.integers(0, N, 12)]).astype(np.uint64)
+        assert np.array_equal(c[idx.astype(np.int64)], oracle.conv_entries(a, b, m, idx).astype(np.uint32)), i
+    # every output at once, item by item: their sum is the product of the operands' sums
+    s = [(t.to(torch.int64) & 0xFFFFFFFF).sum(1) % m for t in (f, g, h)]
+    assert torch.equal(s[2], s[0] * s[1] % m)
+    assert int(h.max()) < m and int(h.min()) >= 0
+
+
+# ---------------------------------------------------------------- several passes
+# words of the batch per pass of all workgroups: 3 * 256 * 4096
+@pytest.mark.parametrize("n", [5, 7, 8])
+@pytest.mark.parametrize("passes,extra", [(2, 3), (3, 4099), (4, 100003)])
+def test_several_passes(nt, n, passes, extra):
+    """Convolutions, quotients and integers of 2^5 .. 2^8 whose workgroups take several
+    passes, the last one a part of one, against the same items in shares of one pass."""
+    share = (3 * 256 * 4096 >> n) - 5
+    count = (passes * 3 * 256 * 4096 >> n) + extra
+    if passes == 4:
+        count = max(count, 100003)
+    f, g = words(10 * n + passes, count, 1 << n), words(20 * n + passes, count, 1 << n)
+
+    def pieces(fn):
+        return torch.cat([fn(f[i:i + share].contiguous(), g[i:i + share].contiguous()) for i in range(0, count, share)])
+
+    items = (0, 1, 4096 >> n, count // 2, count - 2, count - 1)
+    h = batch(nt, f, g, n, M)
+    assert torch.equal(h, pieces(lambda a, b: batch(nt, a, b, n, M)))
+    check_convolutions(h, f, g, M, items)
+    a = f.clone()                                       # over f
+    order = nt.modulus_order(M)
+    nt.conv_batched(a.view(-1), g.view(-1), nt.BatchDesc(np.full(count, n), np.arange(count, dtype=np.int64) << n), M,
+                    root=nt.euler_root(M, order), root_log2order=order, out=a.view(-1), flags=nt.FLAG_EULER)
+    assert torch.equal(a, h)
+    # integers: 15-bit operands, whose sums stay below 2^38
+    f, g = f & 0x7FFF, g & 0x7FFF
+    c = nt.conv_crt(f, g)
+    assert torch.equal(c, pieces(nt.conv_crt))
+    assert torch.equal(c.sum(1), f.to(torch.int64).sum(1) * g.to(torch.int64).sum(1))
+    for i in items:
+        assert np.array_equal(host(c[i]), oracle.conv_integer(host(f[i]), host(g[i])))
+    # quotients: the g of f * g, from divisors whose spectra have no zero
+    F = reduced(f, M - 1) + 1
+    f, g = nt.ntt_inverse(F, M), reduced(g, M)
+    h = batch(nt, f, g, n, M)
+    assert torch.equal(nt.deconvolve(f, h, M), g)
+    F[count - 1, (1 << n) - 1] = 0
+    with pytest.raises(nt.NttError) as e:
+        nt.deconvolve(nt.ntt_inverse(F, M), h, M)
+    assert e.value.name == "NTT_E_SINGULAR"
