@@ -103,3 +103,41 @@ def test_several_passes(nt, n, passes, extra):
     with pytest.raises(nt.NttError) as e:
         nt.deconvolve(nt.ntt_inverse(F, M), h, M)
     assert e.value.name == "NTT_E_SINGULAR"
+
+
+# ---------------------------------------------------------------- long transforms
+def transforms(nt, n, rows, m):
+    N, w = 1 << n, nt.euler_root(m, n)
+    x = words(100 * n + rows, rows, N)
+    before = nt.launch_counts()["matrix_transform"]
+    X, Y = nt.ntt_forward(x, m, w, flags=nt.FLAG_EULER), nt.ntt_inverse(x, m, w, flags=nt.FLAG_EULER)
+    assert nt.launch_counts()["matrix_transform"] == before + 2
+    canon = reduced(x, m)
+    assert torch.equal(nt.ntt_inverse(X, m, w, flags=nt.FLAG_EULER), canon)
+    assert torch.equal(nt.ntt_forward(Y, m, w, flags=nt.FLAG_EULER), canon)
+    rng = np.random.default_rng(n)
+    some = sorted({0, rows // 2, rows - 1, int(rng.integers(0, rows))})
+    bins = np.concatenate([np.tile(np.array([0, 1, 15, 16, 255, 256, N // 2, N - 1], np.uint64), (len(some), 1)),
+                           rng.integers(0, N, (len(some), 16)).astype(np.uint64)], axis=1)
+    at, xs = bins.astype(np.int64), np.stack([host(canon[r]) for r in some])
+    got = np.take_along_axis(np.stack([host(X[r]) for r in some]), at, axis=1)
+    assert np.array_equal(got, oracle.ntt_bins_rows(xs, m, w, bins).astype(np.uint32))
+    got = np.take_along_axis(np.stack([host(Y[r]) for r in some]), at, axis=1)
+    inv = oracle.ntt_bins_rows(xs, m, pow(w, m - 2, m), bins).astype(np.uint64)
+    assert np.array_equal(got, (inv * np.uint64(pow(N, m - 2, m)) % np.uint64(m)).astype(np.uint32))
+    for r in some:                                      # one row takes 16 columns to a workgroup
+        one = x[r:r + 1].contiguous()
+        assert torch.equal(nt.ntt_forward(one, m, w, flags=nt.FLAG_EULER)[0], X[r])
+        assert torch.equal(nt.ntt_inverse(one, m, w, flags=nt.FLAG_EULER)[0], Y[r])
+    z = x.clone()                                       # in place
+    nt.ntt_forward(z, m, w, out=z, flags=nt.FLAG_EULER)
+    assert torch.equal(z, X)
+
+
+@pytest.mark.parametrize("n", range(13, 20))
+@pytest.mark.parametrize("which", ["below", "at", "two chunks"])
+def test_long_transforms_by_rows(nt, n, which):
+    """One row less than 32 columns to a workgroup ask for, as many, and one more than
+    128 MiB of scratch hold."""
+    at = WIDE_BLOCKS >> (n - 12)
+    transforms(nt, n, {"below": at - 1, "at": at, "two chunks": ((1 << 25) >> n) + 1}[which], M)
