@@ -141,3 +141,62 @@ def test_long_transforms_by_rows(nt, n, which):
     128 MiB of scratch hold."""
     at = WIDE_BLOCKS >> (n - 12)
     transforms(nt, n, {"below": at - 1, "at": at, "two chunks": ((1 << 25) >> n) + 1}[which], M)
+
+
+@pytest.mark.parametrize("m", sorted(SMALL))
+@pytest.mark.parametrize("n", range(13, 19))
+def test_long_transforms_small_moduli(nt, n, m):
+    if n > SMALL[m]:
+        pytest.skip("no transform of this length modulo m")
+    for rows in (1, 3, (WIDE_BLOCKS >> (n - 12)) + 1):
+        transforms(nt, n, rows, m)
+
+
+# ---------------------------------------------------------------- three launches
+THREE = [(n, m) for m in sorted(SMALL) for n in range(14, SMALL[m] + 1)] + [(n, M) for n in (14, 15, 16, 17, 19)]
+
+
+def three_counts(n):
+    """Few items; just past the switch to 32 columns in the last launch (2^14 has no such
+    count: 128 items and more go one to a workgroup)."""
+    return (3, 127) if n == 14 else (3, (WIDE_BLOCKS >> (n - 12)) + 1)
+
+
+@pytest.mark.parametrize("n,m", THREE)
+def test_three_launches_by_count(nt, n, m):
+    N = 1 << n
+    for count in three_counts(n):
+        f, g = words(300 * n + count, count, N), words(400 * n + count, count, N)
+        before = nt.launch_counts()["matrix_three"]
+        h = batch(nt, f, g, n, m)
+        assert nt.launch_counts()["matrix_three"] == before + 1
+        check_convolutions(h, f, g, m, (0, count // 2, count - 1))
+        assert torch.equal(h, batch(nt, f, g, n, m, flags=nt.FLAG_PER_ITEM))
+        # the items in another order: through their offsets
+        assert torch.equal(h, batch(nt, f, g, n, m, offs=np.arange(count, dtype=np.int64)[::-1] << n))
+        for a, b in ((0x7F7F7F7F, 0x80808080), (0xFFFFFFFF, 0xFFFFFFFF), (m - 1, m - 1)):
+            F, G = (torch.full((count, N), c - (c >> 31 << 32), dtype=torch.int32, device="cuda") for c in (a, b))
+            assert bool((batch(nt, F, G, n, m) == N * a * b % m).all()), (hex(a), hex(b))
+
+
+@pytest.mark.parametrize("n,m", THREE)
+def test_quotients_by_rows(nt, n, m):
+    N, w = 1 << n, nt.euler_root(m, n)
+    kw = dict(flags=nt.FLAG_EULER)
+    for rows in three_counts(n):
+        F = reduced(words(500 * n + rows, rows, N), m - 1) + 1
+        F[0] = m - 1
+        g = reduced(words(600 * n + rows, rows, N), m)
+        g[-1] = m - 1
+        f = nt.ntt_inverse(F, m, w, **kw)
+        G = nt.ntt_forward(g, m, w, **kw)
+        h = nt.ntt_inverse((G.to(torch.int64) * F % m).to(torch.int32), m, w, **kw)
+        before = nt.launch_counts()["matrix_three"]
+        assert torch.equal(nt.deconvolve(f, h, m, w, **kw), g), rows
+        assert nt.launch_counts()["matrix_three"] == before + 1
+        for r, u in ((0, 0), (rows - 1, N - 1)):
+            Z = F.clone()
+            Z[r, u] = 0
+            with pytest.raises(nt.NttError) as e:
+                nt.deconvolve(nt.ntt_inverse(Z, m, w, **kw), h, m, w, **kw)
+            assert e.value.name == "NTT_E_SINGULAR", (rows, r)
