@@ -6,16 +6,33 @@ namespace nttmi {
 template <class W, int OP>
 static hipError_t conv_fused_t(int logn, const void* f, const void* g, void* h, const uint64_t* offs,
                                uint32_t count, void* scratch, uint32_t* queue, uint32_t grid, const DevPlan& p,
-                               hipStream_t st, uint32_t* singular, CrtStore crt = CrtStore{}) {
+                               hipStream_t st, uint32_t* singular) {
     using T = typename W::word;
     using SW = typename W::sword;
     switch (logn) {
 #define CASE(n)                                                                                                   \
     case n:                                                                                                       \
         hipLaunchKernelGGL((k_conv_fused<W, n, OP>), dim3(grid), dim3(FS<n>::T), 0, st, (const T*)f, (const T*)g, \
-                           (T*)h, offs, count, (SW*)scratch, queue, p, singular, crt);                            \
+                           (T*)h, offs, count, (SW*)scratch, queue, p, singular, CrtStore{});                     \
         return hipGetLastError();
         NTT_LARGE_CASES(CASE)
+#undef CASE
+        default:
+            return hipErrorInvalidValue;
+    }
+}
+
+// The combining store: lengths 2^14 .. 2^16 (others have theirs in other kernels).
+static hipError_t conv_fused_crt(int logn, const void* f, const void* g, uint32_t count, void* scratch, uint32_t* queue,
+                                 uint32_t grid, const DevPlan& p, hipStream_t st, const CrtStore& crt) {
+    switch (logn) {
+#define CASE(n)                                                                                                   \
+    case n:                                                                                                       \
+        hipLaunchKernelGGL((k_conv_fused<W32, n, OP_CRT>), dim3(grid), dim3(FS<n>::T), 0, st, (const uint32_t*)f, \
+                           (const uint32_t*)g, (uint32_t*)nullptr, (const uint64_t*)nullptr, count,               \
+                           (W32::sword*)scratch, queue, p, (uint32_t*)nullptr, crt);                              \
+        return hipGetLastError();
+        CASE(14) CASE(15) CASE(16)
 #undef CASE
         default:
             return hipErrorInvalidValue;
@@ -27,8 +44,8 @@ hipError_t launch_conv_fused(int wbits, int logn, const void* f, const void* g, 
                              hipStream_t st, uint32_t* singular, const CrtStore* crt) {
     if (count == 0) return hipSuccess;
     if (crt) {
-        if (wbits != 32 || singular) return hipErrorInvalidValue;
-        return conv_fused_t<W32, OP_CRT>(logn, f, g, h, offs, count, scratch, queue, grid, p, st, nullptr, *crt);
+        if (wbits != 32 || singular || offs) return hipErrorInvalidValue;
+        return conv_fused_crt(logn, f, g, count, scratch, queue, grid, p, st, *crt);
     }
     if (singular)
         return wbits == 32
