@@ -584,7 +584,8 @@ ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const
     const ntt_status st = get_buf(caches().work, stream, (size_t)group * 8 << n, &ws);
     if (st != NTT_OK) return st;
     count(NTT_COUNT_MATRIX_THREE);
-    return hip_status(launch_conv_four((int)n, f, g, h, doffs, c, group, ws, p->trans, p->four, s, div, crt));
+    return hip_status(launch_conv_four((int)n, f, g, h, doffs, c, group, ws, (uint32_t)cu_count(), p->trans, p->four, s,
+                                       div, crt));
 }
 
 ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f, const void* g, void* h,
@@ -642,7 +643,7 @@ ntt_status ntt_rows(const Plan* p, uint32_t elem_bits, uint32_t log2n, bool inv,
         const uint32_t k = std::min(chunk, batch - r);
         const char* xr = (const char*)x + (size_t)r * per;
         char* Xr = (char*)X + (size_t)r * per;
-        const hipError_t e = trans ? launch_ntt_trans((int)log2n, xr, Xr, k, ws, p->trans[inv], s)
+        const hipError_t e = trans ? launch_ntt_trans((int)log2n, xr, Xr, k, ws, (uint32_t)cu_count(), p->trans[inv], s)
                                  : launch_ntt_fourstep((int)elem_bits, log2n, inv, xr, Xr, k, ws, p->dev, s,
                                                        (uint32_t)cu_count());
         if (e != hipSuccess) return hip_status(e);
@@ -857,8 +858,8 @@ ntt_status launch_multi(const std::map<uint32_t, std::vector<uint64_t>>& cls,
         const uint32_t c = (uint32_t)cls.at(o.first).size();
         const Plan* p = plans[o.first];
         count(NTT_COUNT_MATRIX_THREE);
-        st = hip_status(launch_conv_four((int)o.first, F, G, H, dblob + o.second, c, four_group(o.first, c), ws, p->trans,
-                                         p->four, s));
+        st = hip_status(launch_conv_four((int)o.first, F, G, H, dblob + o.second, c, four_group(o.first, c), ws,
+                                         (uint32_t)cu_count(), p->trans, p->four, s));
         if (st != NTT_OK) return st;
     }
     return hip_status(launch_conv_multi((int)elem_bits, F, G, H, dblob + task_at, ntasks, dblob, ws, scratch_words, q,
@@ -1111,7 +1112,7 @@ ntt_status conv_circular_noalloc(uint64_t m, uint32_t log2n, uint64_t root, uint
     count(NTT_COUNT_FOURSTEP);
     if (use_four(p, elem_bits, log2n, 1)) {
         count(NTT_COUNT_MATRIX_THREE);
-        return hip_status(launch_conv_four((int)log2n, f, g, h, nullptr, 1, 1, ws, p->trans, p->four, s));
+        return hip_status(launch_conv_four((int)log2n, f, g, h, nullptr, 1, 1, ws, (uint32_t)cu_count(), p->trans, p->four, s));
     }
     return hip_status(launch_conv_fourstep((int)elem_bits, log2n, f, g, h, 1, 0, ws, p->dev, s, nullptr,
                                            (uint32_t)cu_count()));

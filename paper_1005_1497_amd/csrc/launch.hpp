@@ -106,19 +106,20 @@ hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, con
 // Transforms of `rows` rows of length 2^logn (TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N)
 // of 32-bit words back to back, the direction that of p's tables; scratch: rows * N
 // words.  x and X may be the same.
-// The column kernels with 32 columns to a workgroup, not 16: `blocks` of 16 columns that
-// are three or more of the doubled ones per CU of a full chip (256).
-inline bool wide_cols(uint32_t blocks) { return blocks >= 2 * 3 * 256; }
 constexpr int TRANS_MIN_LOG2N = 13, TRANS_MAX_LOG2N = 19;
-hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, void* scratch, const I8Plan& p,
-                            hipStream_t st);
+hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, void* scratch, uint32_t cus,
+                            const I8Plan& p, hipStream_t st);
+// Whether `blocks` of 4096 elements are two for each of the three workgroups that a CU
+// holds: then the column kernels take 32 columns to a workgroup, not 16, and the row
+// kernels two passes.
+inline bool two_each(uint32_t blocks, uint32_t cus) { return blocks >= 2 * 3 * (cus ? cus : 1); }
 // Convolutions of lengths TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N of 32-bit words in three
 // launches per `group` items, at offs[i] or back to back (offs null).  trans: the transforms' plans of the length,
 // forward and inverse; rows: tables of the rows (tab) and twiddles (tti); scratch:
 // min(group, count) * 2N words.  crt: the combining store (h unused; items back to back;
 // moduli from 2^21 on).
 hipError_t launch_conv_four(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count, uint32_t group,
-                            void* scratch, const I8Plan* trans, const I8Plan& rows, hipStream_t st,
+                            void* scratch, uint32_t cus, const I8Plan* trans, const I8Plan& rows, hipStream_t st,
                             const Quotient* div = nullptr, const Combine* crt = nullptr);
 hipError_t launch_ntt_small(int wbits, int logn, bool inv, const void* x, void* X, uint32_t batch, const DevPlan& p,
                             hipStream_t st);

@@ -3,14 +3,14 @@
 
 namespace nttmi {
 
-hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, void* scratch, const I8Plan& p,
-                            hipStream_t st) {
+hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, void* scratch, uint32_t cus,
+                            const I8Plan& p, hipStream_t st) {
     if (rows == 0) return hipSuccess;
     const uint32_t blocks = rows << (logn - 12);   // of 4096 outputs
     switch (logn) {
 #define CASE(n)                                                                                                      \
     case n:                                                                                                          \
-        if (wide_cols(blocks))                                                                                       \
+        if (two_each(blocks, cus))                                                                                   \
             hipLaunchKernelGGL((k_ntt_cols<n, 2>), dim3(blocks / 2), dim3(256), 0, st, (const uint32_t*)x,           \
                                (uint32_t*)scratch, p);                                                               \
         else                                                                                                         \
