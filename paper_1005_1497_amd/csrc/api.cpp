@@ -31,6 +31,7 @@ struct Plan {
     I8Plan four{};           // and the rows of their convolutions
     I8Plan trans[2] = {};    // 2^13 .. 2^19: the transforms', forward and inverse (tab null: none)
     I8Plan i8{};             // (tab null: no such kernel for this plan)
+    bool shared = false;     // dP, dTT and dTT32 are those of the other word width's plan
 };
 
 struct Buf {
@@ -102,7 +103,7 @@ struct OffKeyLess {
 
 struct Caches {
     std::mutex mu;
-    std::map<std::tuple<int, uint64_t, int, uint64_t>, Plan> plans;   // (dev, m, log2n, root)
+    std::map<std::tuple<int, uint64_t, int, uint64_t, int>, Plan> plans;   // (dev, m, log2n, root, word width)
     std::map<std::pair<int, void*>, Buf> work;                        // (dev, stream) -> scratch
     std::map<std::pair<int, void*>, Buf> flag;                        // (dev, stream) -> range flag
     std::map<std::pair<int, void*>, Buf> queue;                       // (dev, stream) -> work queue
@@ -218,10 +219,23 @@ int cu_count() {
     return cu_count_locked(dev);
 }
 
+// Frees what a plan owns.
+void free_plan(const Plan& p) {
+    for (void* t : {(void*)p.dI8, (void*)p.dTrans, (void*)p.dFour})
+        if (t) (void)hipFree(t);
+    if (p.shared) return;
+    for (void* t : {(void*)p.dP, (void*)p.dTT, (void*)p.dTT32})
+        if (t) (void)hipFree(t);
+}
+
 // Device tables of the plan (m, N = 2^log2n, root): the powers root^e mod m,
 // e < N, which are the harmonics of the digital circle (Eq. 5) generated one
-// factor at a time, and for four-step lengths the twiddles root^(+-t1 u2).
-ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Plan** out) {
+// factor at a time, and for four-step lengths the twiddles root^(+-t1 u2); with
+// 32-bit words the matrix-core kernels' tables too.  A plan of the other word width
+// has the former already: they are shared, and while the stream is being captured,
+// which allows no further tables, that plan serves as it is.
+ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, uint32_t elem_bits, void* stream,
+                    const Plan** out) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return NTT_E_DEVICE;
     const uint64_t r = root % m;
@@ -230,23 +244,42 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
     const int l2 = modulus_log2nu(m);
     Caches& c = caches();
     std::lock_guard<std::mutex> g(c.mu);
-    auto key = std::make_tuple(dev, m, (int)log2n, r);
+    auto key = std::make_tuple(dev, m, (int)log2n, r, (int)elem_bits);
     auto it = c.plans.find(key);
     if (it != c.plans.end()) {
         *out = &it->second;
         return NTT_OK;
     }
+    it = c.plans.find(std::make_tuple(dev, m, (int)log2n, r, 96 - (int)elem_bits));
+    const Plan* other = it == c.plans.end() ? nullptr : &it->second;
+    const bool matrix = elem_bits == 32 && m <= I8_MAX_M;
+    if (other && matrix) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) return NTT_E_DEVICE;
+        if (cs != hipStreamCaptureStatusNone) {
+            *out = other;
+            return NTT_OK;
+        }
+    }
     (void)cu_count_locked(dev);   // known from here on: a call that may not allocate asks for it
     const uint64_t N = 1ull << log2n;
-    std::vector<double2> hP(N);
+    std::vector<double2> hP(other && !matrix ? 0 : N);
     uint64_t x = 1 % m;
-    for (uint64_t e = 0; e < N; ++e) {
+    for (uint64_t e = 0; e < hP.size(); ++e) {
         hP[e] = tw_pair(x, m);
         x = mulmod64(x, r, m);
     }
     Plan p;
-    hipError_t he = upload(&p.dP, hP);
-    if (he == hipSuccess && (int)log2n > SMALL_MAX_LOG2N) {
+    hipError_t he = hipSuccess;
+    if (other) {
+        p.shared = true;
+        p.dP = other->dP;
+        p.dTT = other->dTT;
+        p.dTT32 = other->dTT32;
+    } else {
+        he = upload(&p.dP, hP);
+    }
+    if (!other && he == hipSuccess && (int)log2n > SMALL_MAX_LOG2N) {
         const int la = fs_la((int)log2n), lb = (int)log2n - la;
         const uint64_t A = 1ull << la, B = 1ull << lb;
         std::vector<double> tt(N);
@@ -263,7 +296,7 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
     // when 2 has order nu = 2^lnu, else N^(m - 2) (Fermat, m prime)
     const uint64_t ninv = (l2 >= (int)log2n) ? powmod64(2, (1ull << l2) - log2n, m)
                                              : powmod64((1ull << log2n) % m, m - 2, m);
-    if (he == hipSuccess && m <= I8_MAX_M && (int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WIDE_MAX_LOG2N) {
+    if (he == hipSuccess && matrix && (int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WIDE_MAX_LOG2N) {
         auto w = [&](uint64_t e) { return (uint64_t)hP[e].x; };
         const bool wave = (int)log2n <= WAVE_MAX_LOG2N;
         std::vector<int8_t> t = wave ? i8_wave_tables((int)log2n, m, ninv, w, &p.i8.C)
@@ -278,7 +311,7 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
         p.i8.tab = p.dI8;
         p.i8.fwd = p.dI8 + own;
     }
-    if (he == hipSuccess && m <= I8_MAX_M && (int)log2n >= TRANS_MIN_LOG2N && (int)log2n <= TRANS_MAX_LOG2N) {
+    if (he == hipSuccess && matrix && (int)log2n >= TRANS_MIN_LOG2N && (int)log2n <= TRANS_MAX_LOG2N) {
         std::vector<int8_t> t;
         size_t at[2];
         for (int inv = 0; inv < 2; ++inv) {
@@ -299,12 +332,7 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
         }
     }
     if (he != hipSuccess) {
-        if (p.dTrans) (void)hipFree(p.dTrans);
-        if (p.dFour) (void)hipFree(p.dFour);
-        if (p.dP) (void)hipFree(p.dP);
-        if (p.dTT) (void)hipFree(p.dTT);
-        if (p.dTT32) (void)hipFree(p.dTT32);
-        if (p.dI8) (void)hipFree(p.dI8);
+        free_plan(p);
         return hip_status(he);
     }
     (void)lnu;
@@ -321,15 +349,18 @@ ntt_status get_plan(uint64_t m, uint32_t log2n, uint64_t root, int lnu, const Pl
     return NTT_OK;
 }
 
-// The cached plan of (m, N, root) on the current device, or null; allocates
-// nothing (no insertion into any cache).
-const Plan* find_plan(uint64_t m, uint32_t log2n, uint64_t root) {
+// The cached plan of (m, N, root) on the current device, that of the other word
+// width if need be, or null; allocates nothing (no insertion into any cache).
+const Plan* find_plan(uint64_t m, uint32_t log2n, uint64_t root, uint32_t elem_bits) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
     Caches& c = caches();
     std::lock_guard<std::mutex> g(c.mu);
-    auto it = c.plans.find(std::make_tuple(dev, m, (int)log2n, root % m));
-    return it == c.plans.end() ? nullptr : &it->second;
+    for (int bits : {(int)elem_bits, 96 - (int)elem_bits}) {
+        auto it = c.plans.find(std::make_tuple(dev, m, (int)log2n, root % m, bits));
+        if (it != c.plans.end()) return &it->second;
+    }
+    return nullptr;
 }
 
 // (log2 nu, v2) of m if cached, without computing or inserting it.
@@ -665,7 +696,7 @@ ntt_status ntt_any(bool inv, uint64_t m, uint32_t log2n, uint64_t root, uint32_t
         if (st != NTT_OK) return st;
     }
     const Plan* p = nullptr;
-    st = get_plan(m, log2n, root, lnu, &p);
+    st = get_plan(m, log2n, root, lnu, elem_bits, stream, &p);
     if (st != NTT_OK) return st;
     return ntt_rows(p, elem_bits, log2n, inv, x, X, batch, stream);
 }
@@ -1071,7 +1102,7 @@ ntt_status conv_circular(uint64_t m, uint32_t log2n, uint64_t root, uint32_t ele
         if (st != NTT_OK) return st;
     }
     const Plan* p = nullptr;
-    st = get_plan(m, log2n, root, lnu, &p);
+    st = get_plan(m, log2n, root, lnu, elem_bits, stream, &p);
     if (st != NTT_OK) return st;
     return conv_one(p, elem_bits, log2n, f, g, h, stream);
 }
@@ -1095,7 +1126,7 @@ ntt_status conv_circular_noalloc(uint64_t m, uint32_t log2n, uint64_t root, uint
     // the four-step scratch: 2N words of the word width
     const bool fourstep = (int)log2n > SMALL_MAX_LOG2N;
     if (fourstep && 2 * bytes > NOALLOC_SCRATCH_BYTES) return NTT_E_UNSUPPORTED;
-    const Plan* p = find_plan(m, log2n, root);
+    const Plan* p = find_plan(m, log2n, root, elem_bits);
     if (!p) return NTT_E_NOPLAN;
     hipStream_t s = (hipStream_t)stream;
     if (!fourstep) {
@@ -1140,7 +1171,7 @@ ntt_status conv_deconvolve(uint64_t m, uint32_t log2n, uint64_t root, uint32_t e
         if (st != NTT_OK) return st;
     }
     const Plan* p = nullptr;
-    st = get_plan(m, log2n, root, lnu, &p);
+    st = get_plan(m, log2n, root, lnu, elem_bits, stream, &p);
     if (st != NTT_OK) return st;
     void* flag = nullptr;
     st = get_buf(caches().flag, stream, sizeof(uint32_t), &flag);
@@ -1218,12 +1249,15 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     if (st == NTT_OK) st = ntt_euler_root(m2, log2n, &r2);
     if (st != NTT_OK) return st;
     const Plan *p1 = nullptr, *p2 = nullptr;
-    st = get_plan(m1, log2n, r1, l1, &p1);
-    if (st == NTT_OK) st = get_plan(m2, log2n, r2, l2, &p2);
+    st = get_plan(m1, log2n, r1, l1, 32, stream, &p1);
+    if (st == NTT_OK) st = get_plan(m2, log2n, r2, l2, 32, stream, &p2);
     if (st != NTT_OK) return st;
-    // residues mod m1, then the convolution mod m2 and the combination of both
+    // residues mod m1, then the convolution mod m2 and the combination of both: in its
+    // store where the matrix-core tables are (from 2^5 on, but for plans shared under
+    // capture), else in a pass of its own
+    const bool store = p2->i8.tab || p2->four.tab;
     void* tmp = nullptr;
-    st = get_buf(caches().tune, stream, ((int)log2n < WAVE_MIN_LOG2N ? 2 : 1) * in_bytes, &tmp);
+    st = get_buf(caches().tune, stream, (store ? 1 : 2) * in_bytes, &tmp);
     if (st != NTT_OK) return st;
     uint32_t* a1 = (uint32_t*)tmp;
     uint32_t* a2 = a1 + (size_t)batch * N;
@@ -1240,21 +1274,21 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     uint64_t grid = log2n < 14 ? 0 : (uint64_t)std::max(1, cu_count()) * std::max(1, fused_blocks_per_cu(32, (int)log2n));
     const int32_t cb = 2 * (uint64_t)c > m2 ? (int32_t)c - (int32_t)m2 : (int32_t)c;
     const Combine crt{a1, (uint64_t*)h, (uint32_t)m1, cb, (float)(-(double)cb / (double)m2)};
-    if ((int)log2n >= WAVE_MIN_LOG2N && (int)log2n <= WAVE_MAX_LOG2N) {
+    if (store && (int)log2n <= WAVE_MAX_LOG2N) {
         count(NTT_COUNT_SMALL);
         count(NTT_COUNT_MATRIX_SHORT);
         return hip_status(launch_conv_wave((int)log2n, f, g, nullptr, batch, p2->i8, (uint32_t)cu_count(), s, nullptr, &crt));
     }
-    if (log2n == 13) {
+    if (store && log2n == 13) {
         count(NTT_COUNT_FUSED);
         count(NTT_COUNT_MATRIX_ONE);
         return hip_status(launch_conv_wide(13, f, g, nullptr, nullptr, batch, (uint32_t)cu_count(), p2->i8, s, nullptr, &crt));
     }
-    if (log2n >= 14 && (use_four(p2, 32, log2n, batch) || 3ull * batch < 2 * grid)) {
+    if (store && (use_four(p2, 32, log2n, batch) || 3ull * batch < 2 * grid)) {
         count(NTT_COUNT_FUSED);   // (the class of every combining convolution above 2^12)
         return conv_four(p2, log2n, batch, f, g, nullptr, nullptr, s, stream, nullptr, &crt);
     }
-    if (log2n >= 14) {
+    if (store) {
         const uint64_t per_wg = (uint64_t)2 * 4 << log2n;
         grid = std::min<uint64_t>(grid, std::max<uint64_t>(1, (1ull << 30) / per_wg));
         grid = std::min<uint64_t>(grid, batch);
@@ -1294,8 +1328,8 @@ ntt_status conv2d_circular(uint64_t m, uint32_t log2r, uint32_t log2c, uint64_t 
         if (st != NTT_OK) return st;
     }
     const Plan *pr = nullptr, *pc = nullptr;
-    st = get_plan(m, log2r, root_r, lnu, &pr);
-    if (st == NTT_OK) st = get_plan(m, log2c, root_c, lnu, &pc);
+    st = get_plan(m, log2r, root_r, lnu, elem_bits, stream, &pr);
+    if (st == NTT_OK) st = get_plan(m, log2c, root_c, lnu, elem_bits, stream, &pc);
     if (st != NTT_OK) return st;
     void* ws = nullptr;
     st = get_buf(caches().tune, stream, 2 * bytes, &ws);
@@ -1396,7 +1430,8 @@ ntt_status conv_batched(uint64_t m, uint64_t root, uint32_t root_log2order, uint
     if (packed && !(flags & (NTT_FLAG_PER_ITEM | NTT_FLAG_AUTOTUNE))) {
         const uint32_t n = d->log2n[0];
         const Plan* p = nullptr;
-        st = get_plan(m, n, powmod64(root % m, 1ull << (root_log2order - n), m), lnu, &p);
+        st = get_plan(m, n, powmod64(root % m, 1ull << (root_log2order - n), m), lnu, elem_bits,
+                      stream, &p);
         if (st != NTT_OK) return st;
         BatchForm form;
         uint8_t cf = CF_DEFAULT;
@@ -1428,7 +1463,7 @@ ntt_status conv_batched(uint64_t m, uint64_t root, uint32_t root_log2order, uint
         const uint32_t n = kv.first;
         const uint64_t item_root = powmod64(root % m, 1ull << (root_log2order - n), m);
         const Plan* p = nullptr;
-        st = get_plan(m, n, item_root, lnu, &p);
+        st = get_plan(m, n, item_root, lnu, elem_bits, stream, &p);
         if (st != NTT_OK) return st;
         plans[n] = p;
     }
@@ -1562,14 +1597,7 @@ void ntt_release_caches(void) {
     Caches& c = caches();
     std::lock_guard<std::mutex> g(c.mu);
     (void)hipDeviceSynchronize();
-    for (auto& kv : c.plans) {
-        if (kv.second.dP) (void)hipFree(kv.second.dP);
-        if (kv.second.dTT) (void)hipFree(kv.second.dTT);
-        if (kv.second.dTT32) (void)hipFree(kv.second.dTT32);
-        if (kv.second.dI8) (void)hipFree(kv.second.dI8);
-        if (kv.second.dTrans) (void)hipFree(kv.second.dTrans);
-        if (kv.second.dFour) (void)hipFree(kv.second.dFour);
-    }
+    for (auto& kv : c.plans) free_plan(kv.second);
     c.plans.clear();
     for (auto& kv : c.work) if (kv.second.ptr) (void)hipFree(kv.second.ptr);
     c.work.clear();
