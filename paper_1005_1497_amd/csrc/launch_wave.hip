@@ -85,8 +85,7 @@ hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t 
         break;
 #define MID(n, s)                                                                                              \
     case n * 2 + s:                                                                                            \
-        if (words > (1u << 24)) hipLaunchKernelGGL((k_ntt_mid<n, s, 5>), chunks, wg, 0, st, xx, hh, words, p); \
-        else hipLaunchKernelGGL((k_ntt_mid<n, s, 4>), chunks, wg, 0, st, xx, hh, words, p);                    \
+        hipLaunchKernelGGL((k_ntt_mid<n, s>), chunks, wg, 0, st, xx, hh, words, p);                            \
         break;
 #define BOTH(K, n) K(n, 0) K(n, 1)
         BOTH(TINY, 5) BOTH(TINY, 6) BOTH(TINY, 7) BOTH(TINY, 8) BOTH(MID, 9) BOTH(MID, 10) BOTH(MID, 11) BOTH(MID, 12)

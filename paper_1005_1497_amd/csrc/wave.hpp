@@ -410,11 +410,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 }
 
 // 2^9 .. 2^12: inputs p0 + 16 (p1 + R1 p2) with p0 in the registers: 16 consecutive
-// bytes per lane, and a row of 64 in the four waves.  WAVES per SIMD: four, or five
-// from more than 2^24 elements on, which no longer lie in the memory-side cache (2^25.3
-// of 2^9 82 -> 76 us, 2^26 129 -> 120; 2^24 26.2 -> 27.2, one row of 2^12 3.9 -> 4.4).
-template <int n, bool SMALL, int WAVES>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) void k_ntt_mid(const uint32_t* f,
+// bytes per lane, and a row of 64 in the four waves.  Four waves per SIMD: five are even
+// (2^24 elements of 2^9 26.7 against 27.3 us, 2^25.3 77 / 77, 2^26 119 / 121), and spill where
+// the two steps share a loop.
+template <int n, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ntt_mid(const uint32_t* f,
                                                                                            uint32_t* h, uint64_t words,
                                                                                            I8Plan p) {
     constexpr int R1 = (1 << n) / 256, N = 1 << n;
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVE
 #pragma unroll
     for (int k = 0; k < 4; ++k) tw[k] = ld_tw(t + T::TB + (4 * wave + k) * 128, lane);
     const Init ti = init_tight(C), raw = init_raw(ti, C, [&](int) { return c == 0; });
-    // (two loops: with both steps in one, five waves per SIMD spilled up to 12 registers)
+    // (two loops: 106 registers, 116 with both steps in one)
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = fold4_tw(digit_sums<TURN>(V, x[k], raw), tk, C);
 #pragma unroll

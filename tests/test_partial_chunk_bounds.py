@@ -24,8 +24,8 @@ template __global__ void nttmi::k_conv_mid<9, false>(In, In, uint32_t*, uint64_t
 template __global__ void nttmi::k_conv_mid<12, false>(In, In, uint32_t*, uint64_t, I8Plan);
 template __global__ void nttmi::k_div_mid<10, false>(In, In, uint32_t*, uint64_t, I8Plan, Quotient);
 template __global__ void nttmi::k_crt_mid<11>(In, In, uint64_t, I8Plan, Combine);
-template __global__ void nttmi::k_ntt_mid<9, false, 4>(In, uint32_t*, uint64_t, I8Plan);
-template __global__ void nttmi::k_ntt_mid<12, false, 5>(In, uint32_t*, uint64_t, I8Plan);
+template __global__ void nttmi::k_ntt_mid<9, false>(In, uint32_t*, uint64_t, I8Plan);
+template __global__ void nttmi::k_ntt_mid<12, true>(In, uint32_t*, uint64_t, I8Plan);
 """
 # buffer_{load,store}_<type> data, offset, s[a:b], <scalar offset> ...
 ACCESS = re.compile(r"^\s*(buffer_(?:load|store)\S*)\s.*s\[\d+:\d+\],\s*([^\s,]+)", re.M)
