@@ -126,11 +126,13 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
     auto load = [&](const uint32_t* src, uint64_t at, int (&v)[TINY_BLOCKS][4]) {
         const uint64_t a = at < words ? at : 0;
         const auto bu = wave_buf(src + a, at < words ? (uint32_t)(words - a < CH ? words - a : CH) * 4 : 0u);
+        uint32_t ll = lw;
+        asm volatile("" : "+v"(ll));   // (as below)
 #pragma unroll
         for (int b = 0; b < TINY_BLOCKS; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                v[b][i] = (int)ld_word(bu, lw, 256 * b + 16 * i);
+                v[b][i] = (int)ld_word(bu, ll, 256 * b + 16 * i);
     };
     // a workgroup's passes lie together
     const uint64_t first = (uint64_t)bx * (4 * CH) * rounds +
@@ -176,6 +178,8 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
             for (int b = 0; b < TINY_BLOCKS; ++b) valid |= (uint32_t)(at + 256 * b + (c / B) * 16 * B < words) << b;
             point(x, y, C, valid);
         }
+        uint32_t ls = lw;
+        asm volatile("" : "+v"(ls));   // (or each offset is a sum of its own, formed before the loop and held)
 #pragma unroll
         for (int b = 0; b < TINY_BLOCKS; ++b) {
             if constexpr (!Point::DIV) {
@@ -186,15 +190,15 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
             if constexpr (CRT) {
                 const auto ba = wave_buf(crt.a1 + at, bytes);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) a1[i] = ld_word(ba, lw, 256 * b + 16 * i);
+                for (int i = 0; i < 4; ++i) a1[i] = ld_word(ba, ls, 256 * b + 16 * i);
             }
             x[b] = fold4_tw(digit_sums<TURN>(A3, x[b], ti), T2, C);
             const Sums s = digit_sums<KEEP>(A4, x[b], ti);
             x[b] = ROWS ? fold4_w(s, tt[b], C) : fold4_tight(s, C);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (CRT) st_out2(bh, combined<SMALL>(x[b][i], a1[i], crt, C), lw, 256 * b + 16 * i);
-                else st_out(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), lw, 256 * b + 16 * i);
+                if constexpr (CRT) st_out2(bh, combined<SMALL>(x[b][i], a1[i], crt, C), ls, 256 * b + 16 * i);
+                else st_out(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), ls, 256 * b + 16 * i);
             }
         }
     }
@@ -336,14 +340,15 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
     }
     __syncthreads();
     mid_get(xch[2], x, wave, gr, c);
+    const uint32_t ls = keep(lw);   // (or sixteen sums for the stores are formed and held with the loads')
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const Sums s = digit_sums<KEEP>(V, x[k], ti);
         x[k] = ROWS ? fold4_w(s, tt[k], C) : fold4_tight(s, C);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if constexpr (CRT) st_out2(bh, combined<SMALL>(x[k][i], a1[k][i], crt, C), lw, mid_word<n>(k, i));
-            else st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), lw, mid_word<n>(k, i));
+            if constexpr (CRT) st_out2(bh, combined<SMALL>(x[k][i], a1[k][i], crt, C), ls, mid_word<n>(k, i));
+            else st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), ls, mid_word<n>(k, i));
         }
     }
 }
