@@ -160,17 +160,24 @@ ntt_status conv_circular_noalloc(uint64_t m, uint32_t log2n, uint64_t root, uint
  * 2^root_log2order; item i uses root^(2^(root_log2order - log2n[i])), of
  * exact order N_i, so log2n[i] <= root_log2order is required.  The usual choice
  * is root = 2 and root_log2order = log2(ord_m(2)).  Default form:
- *   - one length: lengths up to 2^12 run the LDS kernel (several items per
- *     workgroup); longer lengths run the persistent fused kernel (one item per
- *     workgroup at a time, from a per-stream work queue), except that a batch
- *     whose items are back to back and number fewer than two thirds of that
- *     kernel's resident workgroups runs the multi-launch four-step form,
- *     whose phases spread every item over the chip;
+ *   - one length: lengths up to 2^12 run one launch of kernels that keep an item
+ *     on the chip (several items per workgroup); longer lengths run the persistent
+ *     fused kernel (one item per workgroup at a time, from a per-stream work
+ *     queue), except that a batch whose items are back to back and number fewer
+ *     than two thirds of that kernel's resident workgroups runs the multi-launch
+ *     four-step form, whose phases spread every item over the chip.  With 32-bit
+ *     words and m up to 14,600,000 the matrix-core kernels take, before these,
+ *     items up to 2^12 that lie back to back; 2^13, and 2^14 by half as many items
+ *     as compute units and more, an item in one workgroup; and in three launches
+ *     that spread every item over the chip 2^14 by fewer, 2^15 up to 2^25
+ *     elements, 2^16 up to 2^24, and 2^17 .. 2^19;
  *   - several lengths: one persistent launch covers every length up to 2^19
  *     (32-bit words) or 2^18 (64-bit words), except that a batch with fewer
  *     tasks than two thirds of that kernel's resident workgroups, whose items
  *     of each length above 2^12 lie back to back, runs one launch per length
- *     (each as above); longer lengths run one launch per length.
+ *     (each as above); longer lengths run one launch per length.  Lengths that
+ *     the three launches take run there before the persistent one, from 2^17
+ *     on, and from 2^15 on when the tasks are fewer than those two thirds.
  * A form tuned with NTT_FLAG_AUTOTUNE for the batch's shape replaces the
  * default.  Every form gives the same result.  A call is capturable into a
  * HIP graph on a stream once a call with the same batch shape (lengths, item

@@ -581,7 +581,6 @@ ntt_status check_range(uint32_t wbits, const void* x, uint64_t n, uint64_t m, vo
     return hflag ? NTT_E_RANGE : NTT_OK;
 }
 
-// One convolution of length 2^log2n (plan already built) on the stream.
 // Whether a batch of c convolutions of length 2^n takes the one-workgroup
 // matrix-core kernels.  2^13: always (one item 12.4 -> 11.2 us, 128: 18.9 -> 11.9, 256: 23.2
 // -> 12.8).  2^14: an item takes 22 us however few they are, against 12 us in three
@@ -598,7 +597,9 @@ bool use_wide(const Plan* p, uint32_t elem_bits, uint32_t n, uint32_t c) {
 // 2^16 47 -> 38; 2^24 of 2^16 139 -> 130, 2^25 of 2^15 269 -> 245.  From 2^17 on at every
 // size (2^26 elements of 2^17 550 -> 535, of 2^18 637 -> 540, of 2^19 703 -> 539).  2^15 and 2^16
 // beyond: the persistent kernel, whose workgroups are in different phases at a time,
-// waits less for memory (2^26 elements 450 against 485 us, 510 against 515).
+// waits less for memory (2^26 elements 450 against 485 us, 510 against 515); it takes over
+// at two thirds of its workgroups, 342 items of 2^16, and from 257 on the fp64 four-step
+// launches run, which are even here (257 items 152 against 145 us, 300 167 / 169, 340 185 / 187).
 bool use_four(const Plan* p, uint32_t elem_bits, uint32_t n, uint64_t c) {
     return elem_bits == 32 && p->four.tab && (n >= 17 || (c << n) <= (n == 15 ? 1u << 25 : 1u << 24));
 }
@@ -619,6 +620,7 @@ ntt_status conv_four(const Plan* p, uint32_t n, uint32_t c, const void* f, const
                                        div, crt));
 }
 
+// One convolution of length 2^log2n (plan already built) on the stream.
 ntt_status conv_one(const Plan* p, uint32_t wbits, uint32_t log2n, const void* f, const void* g, void* h,
                     void* stream) {
     hipStream_t s = (hipStream_t)stream;
@@ -1266,7 +1268,7 @@ ntt_status conv_crt(uint32_t log2n, const void* f, const void* g, void* h, uint3
     st = launch_items(log2n, batch, 0, nullptr, p1, 32, (const char*)f, (const char*)g, (char*)a1, s, stream, CF_DEFAULT);
     if (st != NTT_OK) return st;
     // The second convolution's store combines both residues (us, against a pass of its
-    // own: 65536 of 2^8 135 -> 121, 4096 of 2^12 158 -> 129, 1000 of 2^13 90 -> 78).  From 2^14 on it
+    // own: 65536 of 2^8 135 -> 110, 4096 of 2^12 158 -> 131, 1000 of 2^13 90 -> 80).  From 2^14 on it
     // is that of the three-launch form, or with every CU busy, where that form waits for memory, that of
     // the persistent kernel (us, three launches / persistent: 800 of 2^14 203 / 287, 4096 944 /
     // 914; 600 of 2^15 347 / 382, 2048 1042 / 990; 300 of 2^16 367 / 415, 512 574 / 560; 512 of

@@ -90,19 +90,19 @@ hipError_t launch_conv_small(int wbits, int logn, const void* f, const void* g, 
 // The wave kernels (matrix cores): `count` convolutions of length 2^logn
 // (WAVE_MIN_LOG2N .. WAVE_MAX_LOG2N) of 32-bit words back to back.
 // div: the quotients g / f instead (exact deconvolutions); crt: the combining store (h
-// unused; moduli from 2^21 on; in the next launcher 2^13 alone and from 4,400,000 on).
+// unused; moduli from 2^21 on; in the next launcher 2^13 alone, and moduli from 4,400,000 on).
 hipError_t launch_conv_wave(int logn, const void* f, const void* g, void* h, uint32_t count, const I8Plan& p,
                             uint32_t cus, hipStream_t st, const Quotient* div = nullptr, const Combine* crt = nullptr);
-// Forward or inverse transforms of `batch` rows of length 2^logn (WAVE_MIN_LOG2N
-// .. WAVE_MAX_LOG2N) of 32-bit words back to back, natural order.
-hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& p, hipStream_t st);
-// The same for lengths WIDE_MIN_LOG2N and WIDE_MAX_LOG2N, a workgroup per item:
-// items at offs[i], or back to back (offs null), on at most `cus` workgroups of
-// 2^14 at a time.
+// Convolutions (quotients) of 32-bit words of lengths WIDE_MIN_LOG2N and WIDE_MAX_LOG2N,
+// a workgroup per item: items at offs[i], or back to back (offs null), on at most `cus`
+// workgroups of 2^14 at a time.  crt as above.
 constexpr int WIDE_MIN_LOG2N = 13, WIDE_MAX_LOG2N = 14;
 hipError_t launch_conv_wide(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count,
                             uint32_t cus, const I8Plan& p, hipStream_t st, const Quotient* div = nullptr,
                             const Combine* crt = nullptr);
+// Forward or inverse transforms of `batch` rows of length 2^logn (WAVE_MIN_LOG2N
+// .. WAVE_MAX_LOG2N) of 32-bit words back to back, natural order.
+hipError_t launch_ntt_wave(int logn, bool inv, const void* x, void* X, uint32_t batch, const I8Plan& p, hipStream_t st);
 // Transforms of `rows` rows of length 2^logn (TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N)
 // of 32-bit words back to back, the direction that of p's tables; scratch: rows * N
 // words.  x and X may be the same.
@@ -114,9 +114,9 @@ hipError_t launch_ntt_trans(int logn, const void* x, void* X, uint32_t rows, voi
 // kernels two passes.
 inline bool two_each(uint32_t blocks, uint32_t cus) { return blocks >= 2 * 3 * (cus ? cus : 1); }
 // Convolutions of lengths TRANS_MIN_LOG2N .. TRANS_MAX_LOG2N of 32-bit words in three
-// launches per `group` items, at offs[i] or back to back (offs null).  trans: the transforms' plans of the length,
-// forward and inverse; rows: tables of the rows (tab) and twiddles (tti); scratch:
-// min(group, count) * 2N words.  crt: the combining store (h unused; items back to back;
+// launches per `group` items, at offs[i] or back to back (offs null).  trans: the
+// transforms' plans of the length, forward and inverse; rows: tables of the rows (tab)
+// and twiddles (tti); scratch: min(group, count) * 2N words.  crt: the combining store (h unused; items back to back;
 // moduli from 2^21 on).
 hipError_t launch_conv_four(int logn, const void* f, const void* g, void* h, const uint64_t* offs, uint32_t count, uint32_t group,
                             void* scratch, uint32_t cus, const I8Plan* trans, const I8Plan& rows, hipStream_t st,

@@ -141,7 +141,7 @@ __device__ __forceinline__ void cols_block(const uint32_t* src, uint32_t* dst, u
                 else __builtin_amdgcn_raw_buffer_store_b64(r[0], bh, lo * 8, at * 8, 0);
             } else if constexpr (V == 2)
                 __builtin_amdgcn_raw_buffer_store_b64(v2u{o[0], o[1]}, bd, lo * 4, at * 4, 0);
-            else st_out(bd, o[0], lo, at);
+            else st_out<true>(bd, o[0], lo, at);
         }
     }
 }

@@ -15,7 +15,9 @@ namespace nttmi {
 // dropped, by a check that covers the lane's offset and the instruction's constant but not
 // a scalar offset.  Where a chunk may be a part of one, all of the offset is therefore in
 // those two: the accessors below take the lane's word and a constant one (up to 1023 words
-// it is in the instruction itself).
+// it is in the instruction itself).  WHOLE: everything accessed is in the buffer, and the
+// second word may be a scalar (2^24 elements of 2^15, rows in three launches: four
+// registers spilled otherwise, 600 integer convolutions 345 -> 353 us).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buf(const void* p, uint32_t bytes) {
     // (uniform by construction; said so, or the descriptor would be taken lane by lane)
     const uint64_t a = (uint64_t)(uintptr_t)p;
@@ -24,14 +26,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buf(const void* p, uint32
     return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), (short)0,
                                              __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
+template <bool WHOLE = false>
 __device__ __forceinline__ uint32_t ld_word(__amdgpu_buffer_rsrc_t b, uint32_t lane_word, uint32_t word) {
-    return __builtin_amdgcn_raw_buffer_load_b32(b, (lane_word + word) * 4, 0, 0);
+    if constexpr (WHOLE) return __builtin_amdgcn_raw_buffer_load_b32(b, lane_word * 4, word * 4, 0);
+    else return __builtin_amdgcn_raw_buffer_load_b32(b, (lane_word + word) * 4, 0, 0);
 }
+template <bool WHOLE = false>
 __device__ __forceinline__ int ld_raw(__amdgpu_buffer_rsrc_t b, uint32_t lane_word, uint32_t word) {
-    return (int)(ld_word(b, lane_word, word) ^ DIG);
+    return (int)(ld_word<WHOLE>(b, lane_word, word) ^ DIG);
 }
+template <bool WHOLE = false>
 __device__ __forceinline__ void st_out(__amdgpu_buffer_rsrc_t b, uint32_t x, uint32_t lane_word, uint32_t word) {
-    __builtin_amdgcn_raw_buffer_store_b32(x, b, (lane_word + word) * 4, 0, 0);
+    if constexpr (WHOLE) __builtin_amdgcn_raw_buffer_store_b32(x, b, lane_word * 4, word * 4, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(x, b, (lane_word + word) * 4, 0, 0);
 }
 __device__ __forceinline__ void st_out2(__amdgpu_buffer_rsrc_t b, v2u x, uint32_t lane_word, uint32_t word) {
     __builtin_amdgcn_raw_buffer_store_b64(x, b, (lane_word + word) * 8, 0, 0);
@@ -127,12 +134,12 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
         const uint64_t a = at < words ? at : 0;
         const auto bu = wave_buf(src + a, at < words ? (uint32_t)(words - a < CH ? words - a : CH) * 4 : 0u);
         uint32_t ll = lw;
-        asm volatile("" : "+v"(ll));   // (as below)
+        if constexpr (!ROWS) asm volatile("" : "+v"(ll));   // (as below)
 #pragma unroll
         for (int b = 0; b < TINY_BLOCKS; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                v[b][i] = (int)ld_word(bu, ll, 256 * b + 16 * i);
+                v[b][i] = (int)ld_word<ROWS>(bu, ll, 256 * b + 16 * i);
     };
     // a workgroup's passes lie together
     const uint64_t first = (uint64_t)bx * (4 * CH) * rounds +
@@ -179,7 +186,7 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
             point(x, y, C, valid);
         }
         uint32_t ls = lw;
-        asm volatile("" : "+v"(ls));   // (or each offset is a sum of its own, formed before the loop and held)
+        if constexpr (!ROWS) asm volatile("" : "+v"(ls));   // (or each offset is a sum of its own, formed before the loop and held)
 #pragma unroll
         for (int b = 0; b < TINY_BLOCKS; ++b) {
             if constexpr (!Point::DIV) {
@@ -198,7 +205,7 @@ __device__ __forceinline__ void tiny_block(const uint32_t* f, const uint32_t* g,
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if constexpr (CRT) st_out2(bh, combined<SMALL>(x[b][i], a1[i], crt, C), ls, 256 * b + 16 * i);
-                else st_out(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), ls, 256 * b + 16 * i);
+                else st_out<ROWS>(bh, ROWS ? (uint32_t)x[b][i] : out_word<SMALL>(x[b][i], C), ls, 256 * b + 16 * i);
             }
         }
     }
@@ -235,7 +242,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 // waves' four registers each: 16-byte accesses on both sides, the four pieces of
 // a row permuted by two bits of the column so that 16 rows touch every bank.
 // One chunk per workgroup, three workgroups per CU; its loads and those of its
-// matrices go out together.  Bound by vector issue (79 vector and 7 matrix
+// matrices go out together.  Bound by vector issue (82 vector and 7 matrix
 // instructions per element).  2^26 elements, m = 13631489, against the LDS
 // kernel's fp64 butterflies: 2^12 341 -> 240 us, 2^9 290 -> 234 us; 2^18
 // elements 10.7 -> 6.9 and 9.0 -> 7.0 us.  Slower: one wave per chunk with the
@@ -273,16 +280,17 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
     const uint32_t bytes = (uint32_t)(words - at < 4096 ? words - at : 4096) * 4;
     const auto bf = wave_buf(f + at, bytes), bg = wave_buf(g + at, bytes),
                bh = CRT ? wave_buf(crt.h + at, 2 * bytes) : wave_buf(h + at, bytes);
-    const uint32_t lw = (uint32_t)(c + 16 * R1 * 4 * gr) + mid_word<n>(4 * wave, 0);
+    const uint32_t lw = (uint32_t)(c + 16 * R1 * 4 * gr) + (ROWS ? 0 : mid_word<n>(4 * wave, 0));
+    auto at_word = [&](int k, int i) { return mid_word<n>(ROWS ? 4 * wave + k : k, i); };
     v4i x[4], y[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw(bf, lw, mid_word<n>(k, i)) ^ (ROWS ? (int)DIG : 0);
+        for (int i = 0; i < 4; ++i) x[k][i] = ld_raw<ROWS>(bf, lw, at_word(k, i)) ^ (ROWS ? (int)DIG : 0);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y[k][i] = ld_raw(bg, lw, mid_word<n>(k, i)) ^ (ROWS ? (int)DIG : 0);
+        for (int i = 0; i < 4; ++i) y[k][i] = ld_raw<ROWS>(bg, lw, at_word(k, i)) ^ (ROWS ? (int)DIG : 0);
     const I8K C(p.C);
     const v4i* t = (const v4i*)p.tab;
     const Mat W = ld_mat(t + T::W, lane);
@@ -336,19 +344,19 @@ __device__ __forceinline__ void mid_block(const uint32_t* f, const uint32_t* g, 
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a1[k][i] = ld_word(ba, lw, mid_word<n>(k, i));
+            for (int i = 0; i < 4; ++i) a1[k][i] = ld_word(ba, lw, at_word(k, i));
     }
     __syncthreads();
     mid_get(xch[2], x, wave, gr, c);
-    const uint32_t ls = keep(lw);   // (or sixteen sums for the stores are formed and held with the loads')
+    const uint32_t ls = ROWS ? lw : keep(lw);   // (or sixteen sums for the stores are formed and held with the loads')
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const Sums s = digit_sums<KEEP>(V, x[k], ti);
         x[k] = ROWS ? fold4_w(s, tt[k], C) : fold4_tight(s, C);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if constexpr (CRT) st_out2(bh, combined<SMALL>(x[k][i], a1[k][i], crt, C), ls, mid_word<n>(k, i));
-            else st_out(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), ls, mid_word<n>(k, i));
+            if constexpr (CRT) st_out2(bh, combined<SMALL>(x[k][i], a1[k][i], crt, C), ls, at_word(k, i));
+            else st_out<ROWS>(bh, ROWS ? (uint32_t)x[k][i] : out_word<SMALL>(x[k][i], C), ls, at_word(k, i));
         }
     }
 }
@@ -379,7 +387,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 // forward one, because the short pieces lie on the side of the loads (2^26 elements
 // of 2^6: 105 us, the forward half 139; of 2^10: 128 and 188).  Bound by memory from
 // 2^24 elements on (2^26, against the LDS kernel's fp64 butterflies: 2^5 241 -> 145 us,
-// 2^8 103 -> 97, 2^9 124 -> 117; 2^24 elements of 2^8 25 -> 22, of 2^10 36 -> 26, of 2^12 40 -> 27).
+// 2^8 103 -> 100, 2^9 124 -> 119; 2^24 elements of 2^8 25 -> 22, of 2^10 36 -> 27, of 2^12 40 -> 28).
 // N <= 2^8: inputs p0 + B p', register element p', column (s, p0).  One pass per wave:
 // beyond the memory-side cache several passes with the next one's words loaded ahead
 // are slower (2^25.3 elements of 2^8 60 against 64 us).

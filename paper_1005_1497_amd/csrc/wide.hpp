@@ -125,6 +125,8 @@ __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g,
     auto tab = [&](int j) { return ts + T::J + j * T::size(R); };
     const uint32_t lw = (uint32_t)(c + 1024 * gr);
     auto at_word = [&](int q, int k, int i) -> uint32_t { return k * 4096 + i * 256 + (wave * PW + q) * 16; };
+    // (past the last item: empty, at an address whose words are there all the same, since
+    // the scalar offsets are outside the check)
     auto buf = [&](const uint32_t* a, uint32_t item) {
         const uint64_t off = item >= count ? 0 : offs ? offs[item] : (uint64_t)item * G::N;
         return wave_buf(a + off, item < count ? G::N * 4 : 0);
@@ -196,7 +198,7 @@ __device__ __forceinline__ void wide_block(const uint32_t* f, const uint32_t* g,
                     if constexpr (CRT)
                         __builtin_amdgcn_raw_buffer_store_b64(combined<MODE != 0>(r[i], a1[k][q][i], crt, C), bh, lw * 8,
                                                               at_word(q, k, i) * 8, 0);
-                    else st_out(bh, out_word<MODE != 0>(r[i], C), lw, at_word(q, k, i));
+                    else st_out<true>(bh, out_word<MODE != 0>(r[i], C), lw, at_word(q, k, i));
                 }
             }
             if (k + 1 < R)
