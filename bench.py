@@ -419,8 +419,9 @@ def _time_ms(fn, reps, stream):
 
 def uneven_bench(args):
     """10000 convolutions of lengths 2^n, n uniform in [6, 19], m = 13631489,
-    packed back to back: one conv_batched call as a single persistent launch,
-    against one launch per length class and one launch sequence per item."""
+    packed back to back: one conv_batched call in its default form (the longest
+    lengths in launches of their own, then a single persistent launch), against
+    one launch per length class and one launch sequence per item."""
     import torch
     import paper_1005_1497_amd as nt
     import seeded_inputs as si
@@ -522,9 +523,8 @@ def single_bench(args):
 def variant_bench(args):
     """The adjacent transforms on the headline shape, 4096 x N = 2^16:
     deconv  exact deconvolution g = inverse(forward(h) / forward(f)),
-            m = 13631489 (rows in 1 GiB scratch chunks, four-step launches,
-            Fermat inverses), against conv_circular-style convolution of the
-            same rows through the same launches (flag FLAG_PER_CLASS form);
+            m = 13631489 (one persistent launch, the divisors of a work item
+            inverted together);
     euler   the batch convolution with the Euler-form prime 7340033 = 7*2^20+1
             and a root of order 2^16 that is not a power of two;
     u64     the batch convolution with 64-bit words and the 45-bit Rader prime

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 // waves' four registers each: 16-byte accesses on both sides, the four pieces of
 // a row permuted by two bits of the column so that 16 rows touch every bank.
 // One chunk per workgroup, three workgroups per CU; its loads and those of its
-// matrices go out together.  Bound by vector issue (82 vector and 7 matrix
+// matrices go out together.  Bound by vector issue (81 vector and 7 matrix
 // instructions per element).  2^26 elements, m = 13631489, against the LDS
 // kernel's fp64 butterflies: 2^12 341 -> 240 us, 2^9 290 -> 234 us; 2^18
 // elements 10.7 -> 6.9 and 9.0 -> 7.0 us.  Slower: one wave per chunk with the
